@@ -28,8 +28,8 @@ struct LayerW {
 
 struct GemmPlan {
     int n_tiles = 0;   // 32-row tiles
-    int mfma = 0;      // MFMA kernel (bf16 weights, K % 32 == 0) or VALU
-    int rb = 0;        // MFMA: 16-row blocks per row group
+    int mfma = 0;      // packed weights and split-layout activations (bf16 and int8 weights, K % 32 == 0)
+    int rb = 0;        // 16-row blocks per row group (0: the VALU kernel)
     int n_groups = 0;  // row groups (VALU: tiles)
     int ks = 1;        // K splits per row group (residual projections)
 };
@@ -167,6 +167,25 @@ GemmPlan make_plan(int n_tiles, int K, int mfma, bool resid, int n_cu)
     return p;
 }
 
+// fp32 weights: the same groups and splits over 16-column steps.  Groups of 2
+// blocks where 4-block ones would leave most CUs without a unit (small
+// models, whose launches are bound by latency).
+GemmPlan make_plan_f32(int n_tiles, int K, bool resid, int n_cu)
+{
+    GemmPlan p;
+    p.n_tiles = n_tiles;
+    const int blocks = 2 * n_tiles, S = K / 16, nw = 4;
+    auto splits = [&](int groups) {
+        if (!resid) return 1;
+        const int ks = std::max(1, (n_cu + groups / 2) / groups);
+        return std::min({ks, std::max(1, S / (4 * nw)), 16});
+    };
+    p.rb = blocks % 4 == 0 && blocks / 4 * splits(blocks / 4) >= n_cu / 2 ? 4 : 2;
+    p.n_groups = blocks / p.rb;
+    p.ks = splits(p.n_groups);
+    return p;
+}
+
 int gemm_units(const GemmPlan &p) { return p.n_groups * p.ks; }
 
 // A projection without K splits whose 4-block groups outnumber the CUs runs
@@ -270,16 +289,10 @@ int enqueue_forward(dv_handle *h, const dv_kv *kv, float *out_logits, bool with_
     // tile-aligned ranges, one workgroup each, so that heads x splits covers
     // the compute units once (each workgroup streams its range with a
     // two-tile pipeline per wave); the last split of a head to finish merges
-    // them (bf16 cache; the fp32 path uses the merge kernel), and a single
-    // split writes the output itself
+    // them, and a single split writes the output itself
     const int total = P + M;
-    int kps, n_split;
-    if (h->bf16) {
-        n_split = std::max(1, std::min(h->n_cu / H, h->attn_split_max));
-        kps = round_up(ceil_div(total, n_split), DV_ATTN_TILE);
-    } else {
-        kps = round_up(ceil_div(total, h->attn_split_max), DV_ATTN_TILE);
-    }
+    int n_split = std::max(1, std::min(h->n_cu / H, h->attn_split_max));
+    const int kps = round_up(ceil_div(total, n_split), DV_ATTN_TILE);
     n_split = ceil_div(total, kps);
 
     GemmArgs g{};
@@ -382,8 +395,6 @@ int enqueue_forward(dv_handle *h, const dv_kv *kv, float *out_logits, bool with_
         aa.vc = g.vc;
         prof_begin(h, DV_K_ATTN);
         hipError_t e = launch_attention(aa, h->bf16, s);
-        // (the bf16 kernel merges its splits itself)
-        if (e == hipSuccess && n_split > 1 && !h->bf16) e = launch_attn_merge(aa, Mpad, s);
         prof_end(h);
         if (e != hipSuccess) return hip_fail(h, e, "attention launch");
         if ((rc = gemm(h->p_o, EPI_RESID, w.wo, nullptr, nullptr, w.pk_o, w.ps_o, d, d, h->attn, h->attn_s, nullptr,
@@ -827,11 +838,14 @@ int dv_verify_init(const dv_config *cfg, const dv_weights *w, void *stream, dv_h
             h->n_cu = ncu;
     }
     const int mf_down = mf && (F % 32 == 0);
-    h->p_qkv = make_plan(3 * d / DV_GEMM_TILE, d, mf, false, h->n_cu);
-    h->p_o = make_plan(d / DV_GEMM_TILE, d, mf, true, h->n_cu);
-    h->p_gu = make_plan(F / 16, d, mf, false, h->n_cu);
-    h->p_down = make_plan(d / DV_GEMM_TILE, F, mf_down, true, h->n_cu);
-    h->p_lm = make_plan(V / DV_GEMM_TILE, d, mf, false, h->n_cu);
+    auto plan = [&](int n_tiles, int K, int mfma, bool resid) {
+        return h->wkind == W_F32 ? make_plan_f32(n_tiles, K, resid, h->n_cu) : make_plan(n_tiles, K, mfma, resid, h->n_cu);
+    };
+    h->p_qkv = plan(3 * d / DV_GEMM_TILE, d, mf, false);
+    h->p_o = plan(d / DV_GEMM_TILE, d, mf, true);
+    h->p_gu = plan(F / 16, d, mf, false);
+    h->p_down = plan(d / DV_GEMM_TILE, F, mf_down, true);
+    h->p_lm = plan(V / DV_GEMM_TILE, d, mf, false);
 
     // split-K partials: units x rb x (64 tokens / 16) x 64 lanes x 4 floats
     size_t part_elems = 16;
@@ -907,17 +921,27 @@ int dv_verify_init(const dv_config *cfg, const dv_weights *w, void *stream, dv_h
             return set_err(nullptr, DV_EHIP, "rope table upload failed");
         }
     }
-    // MFMA path: keep the projection matrices in tile order (one extra copy of
-    // the projection weights in HBM, written once here)
-    if (mf) {
+    // keep the projection matrices in block order (one extra copy of the
+    // projection weights in HBM, written once here).  The fp32 kernel can
+    // also read the caller's rows (at half the rate): the copy of fp32 weights
+    // is made only while it takes at most half of the free memory, so that
+    // models which filled the card without it still do.
+    bool packed = mf;
+    if (h->wkind == W_F32) {
+        const double need = 4.0 * ((double)c.n_layers * (4.0 * d * d + 3.0 * d * F) + (double)V * d);
+        size_t free_b = 0, total_b = 0;
+        packed = hipMemGetInfo(&free_b, &total_b) == hipSuccess && need <= 0.5 * (double)free_b;
+    }
+    if (packed) {
         // int8: the weights keep one byte each and the row scales follow the
         // packed row order
         auto pack = [&](const GemmPlan &p, int epi, const void *w0, const void *w1, const void *w2,
                         const float *s0, const float *s1, const float *s2, int N, int K, uint16_t **dst,
                         float **sdst) -> bool {
-            if (!p.mfma) return true;
+            if (!p.rb) return true;  // the VALU kernel reads the caller's rows
             const size_t elems = (size_t)p.n_tiles * DV_GEMM_TILE * K;
-            if (hipMalloc((void **)dst, elems * (h->wkind == W_I8 ? 1 : 2)) != hipSuccess) return false;
+            const size_t wsz = h->wkind == W_I8 ? 1 : (h->wkind == W_BF16 ? 2 : 4);
+            if (hipMalloc((void **)dst, elems * wsz) != hipSuccess) return false;
             GemmArgs a{};
             a.w0 = w0;
             a.w1 = w1;

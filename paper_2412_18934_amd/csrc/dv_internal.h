@@ -9,7 +9,9 @@
 #define DV_GEMM_TILE 32     // logical output rows per workgroup tile
 #define DV_ATTN_TILE 32     // keys per attention tile
 
-#define DV_ATTN_SPLIT_KEYS 256   // keys per workgroup of the fp32-cache attention
+// attention partials are sized for splits of at least this many keys (and for
+// 512 workgroups over the heads)
+#define DV_ATTN_SPLIT_KEYS 256
 
 // Per-step description of the draft tree (host side; the kernels receive
 // the parts they need by value in their arguments, so no kernel reads it
@@ -75,21 +77,24 @@ enum GemmEpi { EPI_QKV = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_LOGITS = 3, EPI_P
 // l%16, columns 64 p + 8 (l/16) .. +8 in bytes 0-7 and 64 p + 32 + 8 (l/16)
 // .. +8 in bytes 8-15 -- starts at byte ((p G + g) rb + b) 1024; the row
 // scales follow the packed row order (block gb = g rb + b, row r at gb 16 + r).
+// fp32 weights use 16-column steps: the 1 KB block of (step s, block gb) --
+// 16 rows x 16 columns, lane l holding row l%16, columns 16 s + 4 (l/16) .. +4
+// -- starts at float (s 2 n_tiles + gb) 256.
 enum WeightKind { W_F32 = 0, W_BF16 = 1, W_I8 = 2 };
 
 struct GemmArgs {
     const void *w0, *w1, *w2;  // QKV: wq, wk, wv; SWIGLU: w_gate, w_up; else w0
-    const uint16_t *packed;    // MFMA path: the weights in block order (above)
+    const uint16_t *packed;    // the weights in block order (above); null: rows (VALU kernel, fp32 without a copy)
     const float *s0, *s1, *s2; // int8: per-row scales of w0, w1, w2 (packing only)
     const float *scale;        // int8: the row scales in packed row order
     int32_t N;                 // rows of one matrix (d_model, d_ffn or vocab)
     int32_t K;                 // reduction length (row length of the matrices)
     int32_t n_tiles;           // 32-row tiles (QKV counts the three matrices)
-    int32_t rb;                // MFMA path: 16-row blocks per row group (2 or 4)
-    int32_t n_groups;          // row groups: MFMA 2 n_tiles / rb; VALU n_tiles
-    int32_t ks;                // K splits per row group (RESID, MFMA path only)
+    int32_t rb;                // 16-row blocks per row group (2, 4 or 8; VALU: unused)
+    int32_t n_groups;          // row groups: 2 n_tiles / rb; VALU n_tiles
+    int32_t ks;                // K splits per row group (RESID; VALU: 1)
     int32_t n_units;           // n_groups * ks
-    const float *x;            // VALU path: activations [Mpad][K], fp32
+    const float *x;            // fp32 weights and VALU path: activations [Mpad][K], fp32
     const uint16_t *xs;        // MFMA path: the same activations in split layout
     int32_t M, Mpad;
     int32_t half;              // xs, us and out_split in the half split layout
@@ -205,7 +210,6 @@ hipError_t launch_gemm(const GemmArgs &a, int grid, int epi, int wkind, int use_
                        hipStream_t s, hipEvent_t ev_start, hipEvent_t ev_stop);
 hipError_t launch_embed_norm(const NormArgs &a, int Mpad, int weight_bf16, hipStream_t s);
 hipError_t launch_attention(const AttnArgs &a, int kv_bf16, hipStream_t s);
-hipError_t launch_attn_merge(const AttnArgs &a, int Mpad, hipStream_t s);
 hipError_t launch_accept(const AcceptArgs &a, hipStream_t s);
 hipError_t launch_accept_sampled(const SampleArgs &a, hipStream_t s);
 

@@ -3,13 +3,13 @@
 // Step structure (Section 3.1 of the paper: one forward pass of the target
 // over the candidate tokens, then the acceptance rule):
 //   k_embed_norm     embedding gather + the first RMSNorm
-//   k_proj / k_gemm_valu  weight-streaming projections with fused epilogues:
+//   k_proj / k_proj_f32 / k_gemm_valu  weight-streaming projections with fused epilogues:
 //                      QKV    -> 1/rms, rotary embedding, q store, K/V cache write
 //                      RESID  -> residual add into the fp32 stream (O, down)
 //                                and the next RMSNorm's x * gain and sums of squares
 //                      SWIGLU -> 1/rms, silu(gate) * up
 //                      LOGITS -> 1/rms, logits + per-group argmax
-//   k_attn / merge   tree-masked attention over the cache, split over keys
+//   k_attn_mfma      tree-masked attention over the cache, split over keys
 //   k_accept         vocab-wide argmax reduce + greedy acceptance walk
 //   k_accept_sampled speculative sampling walk over full logits rows (T > 0)
 //   k_kv_commit      in-place compaction of the accepted path
@@ -150,24 +150,27 @@ struct RowMap {
 __device__ __forceinline__ RowMap row_map(const GemmArgs &a, int epi, int t)
 {
     RowMap m;
+    // by value: a choice between members of a would keep the whole struct in
+    // scratch memory
+    const void *w0 = a.w0, *w1 = a.w1, *w2 = a.w2;
     if (epi == EPI_QKV) {
         const int per_seg = a.N / DV_GEMM_TILE;
         const int seg = t / per_seg, tt = t - seg * per_seg;
         const int per_head = a.hd / DV_GEMM_TILE;
         const int h = tt / per_head, j0 = (tt - h * per_head) * 16;
-        const void *w = seg == 0 ? a.w0 : (seg == 1 ? a.w1 : a.w2);
+        const void *w = seg == 0 ? w0 : (seg == 1 ? w1 : w2);
         m.ptr[0] = m.ptr[1] = w;
         m.mat[0] = m.mat[1] = seg;
         m.row0[0] = h * a.hd + j0;
         m.row0[1] = h * a.hd + a.hd / 2 + j0;
     } else if (epi == EPI_SWIGLU) {
-        m.ptr[0] = a.w0;
-        m.ptr[1] = a.w1;
+        m.ptr[0] = w0;
+        m.ptr[1] = w1;
         m.mat[0] = 0;
         m.mat[1] = 1;
         m.row0[0] = m.row0[1] = t * 16;
     } else {
-        m.ptr[0] = m.ptr[1] = a.w0;
+        m.ptr[0] = m.ptr[1] = w0;
         m.mat[0] = m.mat[1] = 0;
         m.row0[0] = t * DV_GEMM_TILE;
         m.row0[1] = t * DV_GEMM_TILE + 16;
@@ -182,64 +185,39 @@ __device__ __forceinline__ float silu(float z) { return z / (1.0f + expf(-z)); }
 // complete sums of one row group's rows for token m.
 
 // 1/rms of each token of the input from the producer's partial sums of
-// squares, in a fixed order: thread 4 m + c sums partials c, c + 4, ...
-// (loads issued together), then the four chains are combined by shuffles.
-// Needs 4 Mpad <= blockDim.x; writes rinv[0..Mpad).
-__device__ __forceinline__ void input_rinv(const GemmArgs &a, float *rinv)
-{
-    constexpr int NJ = 32;  // loads in flight per thread
-    const int tid = threadIdx.x, m = tid >> 2, c = tid & 3;
-    float s = 0.f;
-    if (m < a.Mpad) {
-        const float *p = a.ssq_in + (size_t)m * a.n_ssq_in;
-        for (int base = 0; base < a.n_ssq_in; base += 4 * NJ) {
-            float v[NJ];
+// squares, in a fixed order: TPT threads per token each sum every TPT-th
+// partial, then a butterfly.  In two parts: rinv_load issues a thread's first
+// NJ partials before the weight stream starts (a wave's loads return in order,
+// so they are back before the first weights and waiting for them empties
+// nothing), rinv_finish consumes them once the first weight steps have been
+// requested.  All threads share the work: with 4 threads per token (20 loads
+// each at d = 5120, branched on) one wave's stream started late and the
+// others waited for it at the end.
+template <int NT, int MT> struct Rinv {
+    static constexpr int TPT = NT / (MT == 1 ? 16 : (MT == 2 ? 32 : 64));
+    static constexpr int NJ = TPT >= 16 ? 8 : (TPT >= 8 ? 12 : 24);
+    static __device__ __forceinline__ void load(const GemmArgs &a, float (&v)[NJ])
+    {
+        const int m = threadIdx.x / TPT, c = threadIdx.x % TPT;
+        const float *p = a.ssq_in + (size_t)min(m, a.Mpad - 1) * a.n_ssq_in;
 #pragma unroll
-            for (int j = 0; j < NJ; ++j) {
-                const int i = base + c + 4 * j;
-                v[j] = i < a.n_ssq_in ? p[i] : 0.f;
-            }
+        for (int j = 0; j < NJ; ++j) v[j] = p[min(c + TPT * j, a.n_ssq_in - 1)];
+    }
+    static __device__ __forceinline__ void finish(const GemmArgs &a, const float (&v)[NJ], float *rinv)
+    {
+        const int m = threadIdx.x / TPT, c = threadIdx.x % TPT;
+        float s = 0.f;
 #pragma unroll
-            for (int j = 0; j < NJ; ++j) s += v[j];
+        for (int j = 0; j < NJ; ++j) s += c + TPT * j < a.n_ssq_in ? v[j] : 0.f;
+        if (a.n_ssq_in > TPT * NJ) {
+            const float *p = a.ssq_in + (size_t)min(m, a.Mpad - 1) * a.n_ssq_in;
+            for (int i = c + TPT * NJ; i < a.n_ssq_in; i += TPT) s += p[i];
         }
-    }
-    s += __shfl_xor(s, 1);
-    s += __shfl_xor(s, 2);
-    if (m < a.Mpad && c == 0) rinv[m] = m < a.M ? 1.0f / sqrtf(s / (float)a.dn + a.eps) : 0.f;
-}
-
-// The same 1/rms in two parts, for the projections: rinv_load issues the
-// first NJ partials of each thread before the weight stream starts (loads
-// return in order, so they arrive first and no later wait on them drains the
-// stream); rinv_finish, after the stream, adds the remaining partials in the
-// same order and writes rinv (bit-identical to input_rinv).
-template <int NJ>
-__device__ __forceinline__ void rinv_load(const GemmArgs &a, float (&v)[NJ])
-{
-    const int tid = threadIdx.x, m = tid >> 2, c = tid & 3;
-    const float *p = a.ssq_in + (size_t)m * a.n_ssq_in;
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-        const int i = c + 4 * j;
-        v[j] = (m < a.Mpad && i < a.n_ssq_in) ? p[i] : 0.f;
+        for (int off = 1; off < TPT; off <<= 1) s += __shfl_xor(s, off);
+        if (m < a.Mpad && c == 0) rinv[m] = m < a.M ? 1.0f / sqrtf(s / (float)a.dn + a.eps) : 0.f;
     }
-}
-
-template <int NJ>
-__device__ __forceinline__ void rinv_finish(const GemmArgs &a, const float (&v)[NJ], float *rinv)
-{
-    const int tid = threadIdx.x, m = tid >> 2, c = tid & 3;
-    float s = 0.f;
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) s += v[j];
-    if (m < a.Mpad) {
-        const float *p = a.ssq_in + (size_t)m * a.n_ssq_in;
-        for (int i = c + 4 * NJ; i < a.n_ssq_in; i += 4) s += p[i];
-    }
-    s += __shfl_xor(s, 1);
-    s += __shfl_xor(s, 2);
-    if (m < a.Mpad && c == 0) rinv[m] = m < a.M ? 1.0f / sqrtf(s / (float)a.dn + a.eps) : 0.f;
-}
+};
 
 // Residual projections: x += sums, then the next RMSNorm's numerator
 // u = x * gain (split layout or fp32) and the group's sums of squares.
@@ -506,6 +484,80 @@ __device__ __forceinline__ bool slot_empty(const u32x4 &r)
     return r[0] == DV_EMPTY_BITS || r[1] == DV_EMPTY_BITS || r[2] == DV_EMPTY_BITS || r[3] == DV_EMPTY_BITS;
 }
 
+// Split-K: count this split's arrival first; the last split to arrive folds,
+// the others publish their partials v (16-byte stores written through to the
+// device-coherent level, cache policy sc1).  The folder takes its own partial
+// from registers and loads the others, reloading a chunk while it still holds
+// the empty-slot pattern (every slot holds it between launches: the folder
+// puts it back after reading), so no split ever waits for its own stores.
+// Element e = tid + NT c of the unit's NE 16-byte partials sits in v[c].
+// Returns whether this workgroup folded (v then holds the sums in split
+// order).
+template <int NE, int NT, int NV>
+__device__ __forceinline__ bool fold_splits(const GemmArgs &a, int unit, int g, int ks, f32x4 (&v)[NV], int &last_s)
+{
+    const int tid = threadIdx.x, KS = a.ks;
+    const __amdgpu_buffer_rsrc_t pr = rsrc_of(a.part);
+    if (tid == 0) {
+        const uint32_t old = __hip_atomic_fetch_add(a.cnt + g, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        last_s = old == (uint32_t)(KS - 1);
+    }
+    __syncthreads();
+    const bool mine = last_s != 0;
+#pragma unroll
+    for (int c = 0; c < NV; ++c) {
+        const int e = tid + NT * c;
+        if (e >= NE) continue;
+        if (!mine) {
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v[c]), pr,
+                                                   (uint32_t)(((size_t)unit * NE + e) * 16), 0, 16);
+            continue;
+        }
+        // fold in split order, loads of 4 splits in flight together
+        f32x4 sum = (f32x4){0.f, 0.f, 0.f, 0.f};
+        for (int k0 = 0; k0 < KS; k0 += 4) {
+            u32x4 raw[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int k = k0 + j;
+                if (k < KS && k != ks)
+                    raw[j] = __builtin_amdgcn_raw_buffer_load_b128(
+                        pr, (uint32_t)(((size_t)(g * KS + k) * NE + e) * 16), 0, 16);
+            }
+            // reload every chunk still empty, all together, until none is
+            for (int it = 0; it < DV_POLL_MAX; ++it) {
+                bool any = false;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) any |= k0 + j < KS && k0 + j != ks && slot_empty(raw[j]);
+                if (!any) break;
+                __builtin_amdgcn_s_sleep(1);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int k = k0 + j;
+                    if (k < KS && k != ks && slot_empty(raw[j]))
+                        raw[j] = __builtin_amdgcn_raw_buffer_load_b128(
+                            pr, (uint32_t)(((size_t)(g * KS + k) * NE + e) * 16), 0, 16);
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int k = k0 + j;
+                if (k >= KS) break;
+                if (k == ks) {
+                    sum += v[c];
+                } else {
+                    sum += __builtin_bit_cast(f32x4, raw[j]);
+                    __builtin_amdgcn_raw_buffer_store_b128(DV_EMPTY_SLOT, pr,
+                                                           (uint32_t)(((size_t)(g * KS + k) * NE + e) * 16), 0, 16);
+                }
+            }
+        }
+        v[c] = sum;
+    }
+    if (mine && tid == 0) __hip_atomic_store(a.cnt + g, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return mine;
+}
+
 #ifndef DV_WEIGHT_NT
 #define DV_WEIGHT_NT 1
 #endif
@@ -551,6 +603,20 @@ __global__ __launch_bounds__(64) void k_pack_blocks_i8(GemmArgs a, int epi, uint
     }
 }
 
+// fp32 weights: the 1 KB block of (16-column step s, block gb) takes 16 bytes
+// of row l % 16 per lane.
+__global__ __launch_bounds__(64) void k_pack_blocks_f32(GemmArgs a, int epi, float *dst)
+{
+    const int gb = blockIdx.x, lane = threadIdx.x;
+    const RowMap rm = row_map(a, epi, gb >> 1);
+    const int h = gb & 1;
+    const float *src = reinterpret_cast<const float *>(rm.ptr[h]) + (size_t)(rm.row0[h] + (lane & 15)) * a.K +
+                       (lane >> 4) * 4;
+    for (int s = blockIdx.y; s < a.K / 16; s += gridDim.y)
+        *reinterpret_cast<float4 *>(dst + ((size_t)s * gridDim.x + gb) * 256 + lane * 4) =
+            *reinterpret_cast<const float4 *>(src + 16 * s);
+}
+
 // Row scales in packed row order: block gb, row r -> dst[16 gb + r].
 __global__ __launch_bounds__(16) void k_pack_scales(GemmArgs a, int epi, float *dst)
 {
@@ -578,7 +644,6 @@ __global__ __launch_bounds__(64 * NW) void k_proj(GemmArgs a)
     constexpr bool HALF = MT_ == 0;
     constexpr int MT = HALF ? 1 : MT_;  // token tiles of the MFMA outputs
     constexpr int ROWS = RB * 16, LD = ROWS + 1, NE = RB * MT * 64;
-    static_assert(64 * NW >= 4 * 16 * MT, "input_rinv needs 4 threads per token");
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, tid = threadIdx.x;
     // a step is one k-step of 32 (bf16 weights) or a pair of them (int8);
     // XP activation blocks per step and token tile (PP parts per k-step)
@@ -600,14 +665,8 @@ __global__ __launch_bounds__(64 * NW) void k_proj(GemmArgs a)
     // loads return in order, so they are back before the first weights and no
     // wait for them empties the stream.
     constexpr bool NEED_RINV = EPI != EPI_RESID && EPI != EPI_PLAIN;
-    constexpr int NJP = MT >= 2 ? 8 : 24;                            // norm partials per thread
+    using RV = Rinv<64 * NW, MT>;
     constexpr int SXN = (16 * MT * ROWS + 64 * NW - 1) / (64 * NW);  // RESID: x values per thread
-    // QKV and gate/up compute the input's 1/rms right after requesting their
-    // first weight steps, so every wave waits for those steps before
-    // streaming on; measured faster than preloading the partials (13B: QKV
-    // 28.0 -> 26.9 us, gate/up 44.5 -> 43.6 us), while lm_head is faster
-    // with the preload (51.4 against 53.2 us)
-    constexpr bool RINV_FIRST = EPI == EPI_QKV || EPI == EPI_SWIGLU;
     static_assert(ROWS <= 64 * NW, "one gain per thread");
 
     for (int unit = blockIdx.x; unit < a.n_units; unit += gridDim.x) {
@@ -630,8 +689,7 @@ __global__ __launch_bounds__(64 * NW) void k_proj(GemmArgs a)
             for (int mt = 0; mt < MT; ++mt) acc[b][mt] = (f32x4){0.f, 0.f, 0.f, 0.f};
         f32x4 rs[Q8 ? RB : 1];  // int8: this lane's four row scales per block
         float sx[EPI == EPI_RESID ? SXN : 1], sgain = 0.f;
-        float sv[NEED_RINV ? NJP : 1];
-        const bool load_rinv = NEED_RINV && !have_rinv;
+        float sv[RV::NJ];
         if constexpr (EPI == EPI_RESID) {
 #pragma unroll
             for (int c = 0; c < SXN; ++c) {
@@ -640,8 +698,8 @@ __global__ __launch_bounds__(64 * NW) void k_proj(GemmArgs a)
             }
             if (tid < ROWS) sgain = Elem<uint16_t>::load(reinterpret_cast<const uint16_t *>(a.gain), g * ROWS + tid);
         }
-        if constexpr (NEED_RINV && !RINV_FIRST) {
-            if (load_rinv) rinv_load<NJP>(a, sv);
+        if constexpr (NEED_RINV) {
+            if (!have_rinv) RV::load(a, sv);
         }
         if (n > 0) {
             u32x4 wb[U][RB], xb[U][MT][XP];
@@ -686,12 +744,11 @@ __global__ __launch_bounds__(64 * NW) void k_proj(GemmArgs a)
                 for (int b = 0; b < RB; ++b)
                     rs[b] = *reinterpret_cast<const f32x4 *>(a.scale + (g * RB + b) * 16 + 4 * (lane >> 4));
             }
-            if constexpr (RINV_FIRST) {
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (NEED_RINV) {
                 // the first unit's weight steps are in flight
-                if (!have_rinv) {
-                    input_rinv(a, rinv);
-                    have_rinv = true;
-                }
+                if (!have_rinv) RV::finish(a, sv, rinv);
+                have_rinv = true;
             }
             int i = 0;
             for (; i + U < n; i += U) {
@@ -725,17 +782,9 @@ __global__ __launch_bounds__(64 * NW) void k_proj(GemmArgs a)
             }
             if (tid < ROWS) stage_s[tid] = sgain;
         }
-        if constexpr (NEED_RINV && !RINV_FIRST) {
-            if (load_rinv) {
-                rinv_finish<NJP>(a, sv, rinv);
-                have_rinv = true;
-            }
-        }
-        if constexpr (RINV_FIRST) {
-            if (!have_rinv) {  // a unit without k-steps for this workgroup's waves
-                input_rinv(a, rinv);
-                have_rinv = true;
-            }
+        if constexpr (NEED_RINV) {
+            if (!have_rinv) RV::finish(a, sv, rinv);  // no k-step of the unit for this wave
+            have_rinv = true;
         }
 
         // wave partials -> unit sums (fixed wave order)
@@ -755,77 +804,7 @@ __global__ __launch_bounds__(64 * NW) void k_proj(GemmArgs a)
                 for (int w = 1; w < NW; ++w) v[c] += red[w][e >> 6][e & 63];
             }
         }
-        bool mine = true;
-        if (KS > 1) {
-            // Count this split's arrival first; the last split to arrive
-            // folds, the others publish their partials (16-byte stores
-            // written through to the device-coherent level, cache policy
-            // sc1).  The folder takes its own partial from registers and
-            // loads the others, reloading a chunk while it still holds the
-            // empty-slot pattern (every slot holds it between launches: the
-            // folder puts it back after reading), so no split ever waits for
-            // its own stores.
-            const __amdgpu_buffer_rsrc_t pr =
-                __builtin_amdgcn_make_buffer_rsrc(a.part, (short)0, 0x7fffffff, 0x00020000);
-            if (tid == 0) {
-                const uint32_t old = __hip_atomic_fetch_add(a.cnt + g, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                last_s = old == (uint32_t)(KS - 1);
-            }
-            __syncthreads();
-            mine = last_s != 0;
-#pragma unroll
-            for (int c = 0; c < (NE + 64 * NW - 1) / (64 * NW); ++c) {
-                const int e = tid + 64 * NW * c;
-                if (e >= NE) continue;
-                if (!mine) {
-                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v[c]), pr,
-                                                           (uint32_t)(((size_t)unit * NE + e) * 16), 0, 16);
-                    continue;
-                }
-                // fold in split order, loads of 4 splits in flight together
-                f32x4 sum = (f32x4){0.f, 0.f, 0.f, 0.f};
-                for (int k0 = 0; k0 < KS; k0 += 4) {
-                    u32x4 raw[4];
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const int k = k0 + j;
-                        if (k < KS && k != ks)
-                            raw[j] = __builtin_amdgcn_raw_buffer_load_b128(
-                                pr, (uint32_t)(((size_t)(g * KS + k) * NE + e) * 16), 0, 16);
-                    }
-                    // reload every chunk still empty, all together, until none is
-                    for (int it = 0; it < DV_POLL_MAX; ++it) {
-                        bool any = false;
-#pragma unroll
-                        for (int j = 0; j < 4; ++j)
-                            any |= k0 + j < KS && k0 + j != ks && slot_empty(raw[j]);
-                        if (!any) break;
-                        __builtin_amdgcn_s_sleep(1);
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) {
-                            const int k = k0 + j;
-                            if (k < KS && k != ks && slot_empty(raw[j]))
-                                raw[j] = __builtin_amdgcn_raw_buffer_load_b128(
-                                    pr, (uint32_t)(((size_t)(g * KS + k) * NE + e) * 16), 0, 16);
-                        }
-                    }
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const int k = k0 + j;
-                        if (k >= KS) break;
-                        if (k == ks) {
-                            sum += v[c];
-                        } else {
-                            sum += __builtin_bit_cast(f32x4, raw[j]);
-                            __builtin_amdgcn_raw_buffer_store_b128(
-                                DV_EMPTY_SLOT, pr, (uint32_t)(((size_t)(g * KS + k) * NE + e) * 16), 0, 16);
-                        }
-                    }
-                }
-                v[c] = sum;
-            }
-            if (mine && tid == 0) __hip_atomic_store(a.cnt + g, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
+        const bool mine = KS == 1 || fold_splits<NE, 64 * NW>(a, unit, g, ks, v, last_s);
         if (mine) {
             if (HALF) {
                 // token n = hi column n + lo column n + 8; columns 8-15 -> 0
@@ -871,7 +850,189 @@ __global__ __launch_bounds__(64 * NW) void k_proj(GemmArgs a)
 }
 
 // ---------------------------------------------------------------------------
-// VALU GEMM (fp32 weights, or bf16 where K is not a multiple of 32).  One
+// Projection for fp32 weights on v_mfma_f32_16x16x4_f32 (fp32 products and
+// sums).  Bound by the weight bytes up to about 32 tokens, by the fp32 matrix
+// rate (256 flop per CU and clock) at 64.
+//
+// A step is 16 columns: lane l holds the 4 consecutive columns 4 (l / 16) ..
+// of weight row l % 16 (one 16-byte load per 16-row block) and the same
+// columns of token l % 16, and MFMA i takes component i of both, i.e. columns
+// 4 g + i, g = 0..3.  The weights come from the packed copy (k-major: the 1 KB
+// block of (step s, block b of NB) at float (s NB + b) 256, lane order) or,
+// where none is kept, from the caller's rows (64 bytes per row and load, a
+// wave taking steps in pairs so that it uses whole 128-byte lines).  Same
+// kernel, other strides; measured on 22016 x 4096 and 12288 x 4096, 16
+// tokens: 5.4 and 6.3 TB/s packed, 3.2 and 3.3 from rows.  Units, K splits,
+// the wave partials' sum in LDS and the epilogues are k_proj's.
+// 7B width, 16 tokens, against the VALU kernel it replaces (8 lanes per row,
+// every row's lanes loading the activations again): QKV 174 -> 38 us, O 106 ->
+// 18, gate/up 243 -> 71, down 275 -> 34, lm_head 318 -> 78.
+template <int MT, int EPI, int NW, int U, int RB>
+__global__ __launch_bounds__(64 * NW) void k_proj_f32(GemmArgs a)
+{
+    constexpr int ROWS = RB * 16, LD = ROWS + 1, NE = RB * MT * 64, NV = (NE + 64 * NW - 1) / (64 * NW);
+    static_assert(ROWS <= 64 * NW, "one gain per thread");
+    constexpr bool NEED_RINV = EPI != EPI_RESID;
+    using RV = Rinv<64 * NW, MT>;
+    constexpr int SXN = (16 * MT * ROWS + 64 * NW - 1) / (64 * NW);  // RESID: x values per thread
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n16 = lane & 15, g4 = lane >> 4;
+    const int K = a.K, S = K / 16, KS = a.ks;
+    __shared__ f32x4 red[NW][NE / 64][64];
+    __shared__ float Y[16 * MT * LD];
+    __shared__ float rinv[DV_TREE_MAX];
+    __shared__ int last_s;
+    __shared__ float stage_s[EPI == EPI_RESID ? ROWS : 1];
+    bool have_rinv = false;
+
+    for (int unit = blockIdx.x; unit < a.n_units; unit += gridDim.x) {
+        const int g = unit / KS, ks = unit - g * KS;
+        const int sb = (ks * S) / KS, T = ((ks + 1) * S) / KS - sb;  // this unit's steps
+        // pairs of steps go round the waves: wave w has steps 2 w, 2 w + 1,
+        // 2 (w + NW), ...
+        const int rem = T % (2 * NW) - 2 * wave;
+        const int n = 2 * (T / (2 * NW)) + (rem < 0 ? 0 : (rem > 2 ? 2 : rem));
+        auto step = [&](int i) { return sb + 2 * NW * (i >> 1) + 2 * wave + (i & 1); };
+        const float *wp[RB];
+        const int xlane = n16 * K + 4 * g4;
+        int wlane = 4 * lane;
+        size_t wstep = (size_t)a.n_tiles * 512;
+#pragma unroll
+        for (int b = 0; b < RB; ++b) wp[b] = reinterpret_cast<const float *>(a.packed) + (size_t)(g * RB + b) * 256;
+        if (!a.packed) {
+            wlane = xlane;
+            wstep = 16;
+#pragma unroll
+            for (int b = 0; b < RB; ++b) {
+                const RowMap rm = row_map(a, EPI, (g * RB + b) >> 1);
+                wp[b] = reinterpret_cast<const float *>(rm.ptr[b & 1]) + (size_t)rm.row0[b & 1] * K;
+            }
+        }
+        f32x4 acc[RB][MT];
+#pragma unroll
+        for (int b = 0; b < RB; ++b)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) acc[b][mt] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        float sx[EPI == EPI_RESID ? SXN : 1], sgain = 0.f;
+        if constexpr (EPI == EPI_RESID) {
+            // the unit's rows of x and their gains arrive before the weights
+#pragma unroll
+            for (int c = 0; c < SXN; ++c) {
+                const int e = tid + 64 * NW * c, m = e / ROWS, r = e - m * ROWS;
+                sx[c] = (e < 16 * MT * ROWS && m < a.M) ? a.resid[(size_t)m * a.N + g * ROWS + r] : 0.f;
+            }
+            if (tid < ROWS) sgain = reinterpret_cast<const float *>(a.gain)[g * ROWS + tid];
+        }
+        float sv[RV::NJ];
+        if constexpr (NEED_RINV) {
+            if (!have_rinv) RV::load(a, sv);
+        }
+        if (n > 0) {
+            f32x4 wb[U][RB], xb[U][MT];
+            auto fetch = [&](int j, int i) {
+                const int st = step(i);
+#pragma unroll
+                for (int b = 0; b < RB; ++b)
+                    wb[j][b] = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(wp[b] + st * wstep + wlane));
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt)
+                    xb[j][mt] = *reinterpret_cast<const f32x4 *>(a.x + (size_t)(16 * mt) * K + 16 * st + xlane);
+            };
+            auto mfma = [&](int j) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int b = 0; b < RB; ++b)
+#pragma unroll
+                        for (int mt = 0; mt < MT; ++mt)
+                            acc[b][mt] =
+                                __builtin_amdgcn_mfma_f32_16x16x4f32(wb[j][b][i], xb[j][mt][i], acc[b][mt], 0, 0, 0);
+            };
+            // U steps in flight (indices past the end re-read the last step
+            // and are dropped)
+#pragma unroll
+            for (int j = 0; j < U; ++j) fetch(j, min(j, n - 1));
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (NEED_RINV) {
+                if (!have_rinv) RV::finish(a, sv, rinv);
+                have_rinv = true;
+            }
+            int i = 0;
+            for (; i + U < n; i += U) {
+#pragma unroll
+                for (int j = 0; j < U; ++j) {
+                    mfma(j);
+                    fetch(j, min(i + j + U, n - 1));
+                    // keep step j's loads ahead of step j + 1's MFMAs
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < U; ++j)
+                if (i + j < n) mfma(j);
+        }
+        if constexpr (EPI == EPI_RESID) {
+#pragma unroll
+            for (int c = 0; c < SXN; ++c) {
+                const int e = tid + 64 * NW * c, m = e / ROWS, r = e - m * ROWS;
+                if (e < 16 * MT * ROWS) Y[m * LD + r] = sx[c];
+            }
+            if (tid < ROWS) stage_s[tid] = sgain;
+        }
+        if constexpr (NEED_RINV) {
+            if (!have_rinv) RV::finish(a, sv, rinv);  // no step of the unit for this wave
+            have_rinv = true;
+        }
+        // wave partials -> unit sums (fixed wave order)
+#pragma unroll
+        for (int b = 0; b < RB; ++b)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) red[wave][b * MT + mt][lane] = acc[b][mt];
+        __syncthreads();
+        f32x4 v[NV];
+#pragma unroll
+        for (int c = 0; c < NV; ++c) {
+            const int e = tid + 64 * NW * c;
+            v[c] = (f32x4){0.f, 0.f, 0.f, 0.f};
+            if (e < NE) {
+                v[c] = red[0][e >> 6][e & 63];
+#pragma unroll
+                for (int w = 1; w < NW; ++w) v[c] += red[w][e >> 6][e & 63];
+            }
+        }
+        const bool mine = KS == 1 || fold_splits<NE, 64 * NW>(a, unit, g, ks, v, last_s);
+        if (mine) {
+            // D layout -> Y[token][row]
+#pragma unroll
+            for (int c = 0; c < NV; ++c) {
+                const int e = tid + 64 * NW * c;
+                if (e < NE) {
+                    const int l = e & 63, bm = e >> 6, b = bm / MT, mt = bm - b * MT;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        float &y = Y[(mt * 16 + (l & 15)) * LD + b * 16 + 4 * (l >> 4) + j];
+                        y = EPI == EPI_RESID ? y + v[c][j] : v[c][j];
+                    }
+                }
+            }
+            __syncthreads();
+            if (EPI == EPI_RESID) {
+                resid_epilogue<float>(a, Y, LD, g * ROWS, ROWS, g, true, stage_s);
+            } else if (EPI == EPI_LOGITS) {
+                logits_epilogue(a, Y, LD, g * ROWS, ROWS, g, rinv);
+            } else if (EPI == EPI_SWIGLU) {
+                swiglu_epilogue(a, Y, LD, g * (RB / 2), RB / 2, rinv);
+            } else {
+#pragma unroll
+                for (int p = 0; p < RB / 2; ++p) qkv_epilogue<float>(a, Y + 32 * p, LD, g * (RB / 2) + p, rinv);
+            }
+        }
+        __syncthreads();
+    }
+}
+
+// ---------------------------------------------------------------------------
+// VALU GEMM: the down projection of bf16 weights whose d_ffn is not a multiple
+// of 32.  One
 // 32-row tile per unit, full K.  Thread (row r = tid/8, lane-in-row kl =
 // tid%8) walks k = 8 kl + 64 i, 8 weights per load; 16 tokens per pass; the 8
 // partial sums of a row are combined with butterfly shuffles.
@@ -899,29 +1060,21 @@ template <> struct Load8<uint16_t> {
     }
 };
 
-template <typename W, int EPI, typename KV>
 __global__ __launch_bounds__(256) void k_gemm_valu(GemmArgs a)
 {
     constexpr int LD = DV_GEMM_TILE + 1;
     const int r = threadIdx.x >> 3, kl = threadIdx.x & 7;
     const int K = a.K;
     __shared__ float Y[DV_TREE_MAX * LD];
-    __shared__ float rinv[DV_TREE_MAX];
-    if (EPI != EPI_RESID) {
-        input_rinv(a, rinv);
-        __syncthreads();
-    }
     for (int t = blockIdx.x; t < a.n_tiles; t += gridDim.x) {
-        const RowMap rm = row_map(a, EPI, t);
-        const int hsel = r >> 4;
-        const W *wrow = reinterpret_cast<const W *>(rm.ptr[hsel]) + (size_t)(rm.row0[hsel] + (r & 15)) * K;
+        const uint16_t *wrow = reinterpret_cast<const uint16_t *>(a.w0) + (size_t)(t * DV_GEMM_TILE + r) * K;
         for (int m0 = 0; m0 < a.Mpad; m0 += 16) {
             float acc[16];
 #pragma unroll
             for (int m = 0; m < 16; ++m) acc[m] = 0.f;
             for (int k = kl * 8; k < K; k += 64) {
                 float w[8];
-                Load8<W>::get(wrow + k, w);
+                Load8<uint16_t>::get(wrow + k, w);
 #pragma unroll
                 for (int m = 0; m < 16; ++m) {
                     float xv[8];
@@ -942,10 +1095,7 @@ __global__ __launch_bounds__(256) void k_gemm_valu(GemmArgs a)
             }
         }
         __syncthreads();
-        if (EPI == EPI_RESID) resid_epilogue<W>(a, Y, LD, t * DV_GEMM_TILE, DV_GEMM_TILE, t, false, nullptr);
-        else if (EPI == EPI_LOGITS) logits_epilogue(a, Y, LD, t * DV_GEMM_TILE, DV_GEMM_TILE, t, rinv);
-        else if (EPI == EPI_SWIGLU) swiglu_epilogue(a, Y, LD, t, 1, rinv);
-        else qkv_epilogue<KV>(a, Y, LD, t, rinv);
+        resid_epilogue<uint16_t>(a, Y, LD, t * DV_GEMM_TILE, DV_GEMM_TILE, t, false, nullptr);
         __syncthreads();
     }
 }
@@ -1034,12 +1184,12 @@ __global__ __launch_bounds__(DV_NORM_THREADS) void k_embed_norm(NormArgs a)
 // cache slots; the tree's own keys/values were written to slots P.. by the
 // QKV epilogue.  Key j is visible to node i iff j < P or bit (j-P) of
 // anc(i).  Each split writes its unnormalised output with the running max
-// and sum; the splits are combined by the last split of the head to finish
-// (bf16 cache) or by k_attn_merge (fp32 cache); with one split the workgroup
-// writes the normalised output itself.
+// and sum; the splits are combined by the last split of the head to finish;
+// with one split the workgroup writes the normalised output itself.
 
-// bf16 cache, MFMA.  Queries are taken 16 at a time; the NW waves take
-// interleaved 32-key tiles and are combined in LDS at the end.
+// Queries are taken 16 at a time; the NW waves take interleaved key tiles and
+// are combined in LDS at the end.
+// bf16 cache, 32-key tiles:
 //   S^T = K Q^T: A = 16 keys x 32 dims (16 bytes of one key row per lane),
 //   B = Q^T (fp32 queries split into bf16 hi + lo, staged in LDS).  Tile "a"
 //   holds keys k0 + 8(r/4) + r%4 in row r, tile "b" the same + 4, so lane l
@@ -1047,6 +1197,13 @@ __global__ __launch_bounds__(DV_NORM_THREADS) void k_embed_norm(NormArgs a)
 //   k0 + 8(l/16) .. +8.
 //   O = P V: A = P (those 8 scores per lane, exponentiated, split hi + lo),
 //   B = V^T rows: 16 bytes = the same 8 consecutive keys of one dim.
+// fp32 cache, 16-key tiles, v_mfma_f32_16x16x4_f32: a lane loads 4 consecutive
+// dims of key row l % 16 (A) and of query l % 16 (B), MFMA i takes component
+// i of both; lane l then holds the scores of query l % 16 for the keys
+// 4 (l / 16) .. +4, which are the A operands of P V as they stand (MFMA j
+// takes keys 4 g + j), with 4 consecutive slots of one dim of V as B.  7B
+// heads, 16 nodes, 512 keys: 13 us (a VALU kernel with tiles in LDS and a
+// separate merge launch: 53 + 6).
 // Scores are kept in base-2 units (scaled by log2(e)/sqrt(hd)) so every
 // exponential is one exp2 (the running max handed to the merge stays in
 // base-2 units).  Each wave keeps two tiles of K and V in
@@ -1058,10 +1215,12 @@ __global__ __launch_bounds__(DV_NORM_THREADS) void k_embed_norm(NormArgs a)
 // leaves room for 8 waves when a split has at most one tile per wave.
 // QT query tiles of 16 are held at once (M <= 16 QT): every loaded key tile
 // serves all of them, each with its own running max, sum and output.
-template <int HD, int NW, bool DB, int QT>
+template <int HD, int NW, bool DB, int QT, typename KV = uint16_t>
 __global__ __launch_bounds__(64 * NW) void k_attn_mfma(AttnArgs a)
 {
-    constexpr int NC = HD / 32;  // QK k-steps over dims
+    constexpr bool F32 = sizeof(KV) == 4;
+    constexpr int TK = F32 ? 16 : 32;  // keys per tile
+    constexpr int NC = HD / 32;  // QK k-steps over dims (bf16)
     constexpr int ND = HD / 16;  // PV output dim tiles
     static_assert(64 * NW >= 2 * HD, "one thread per 8 query values");
     const int split = blockIdx.x, h = blockIdx.y;
@@ -1070,24 +1229,38 @@ __global__ __launch_bounds__(64 * NW) void k_attn_mfma(AttnArgs a)
     const int M = a.tm.M, P = a.tm.P, total = P + M;
     const int kbeg = split * a.keys_per_split;
     const int kend = min(total, kbeg + a.keys_per_split);
-    const int ntile = (kend - kbeg + 31) / 32;
+    const int ntile = (kend - kbeg + TK - 1) / TK;
     const int D = a.H * HD;
     const float scale2 = 1.4426950408889634f / sqrtf((float)HD);
-    const uint16_t *kc = reinterpret_cast<const uint16_t *>(a.kc) + (size_t)h * a.cap * HD;
-    const uint16_t *vc = reinterpret_cast<const uint16_t *>(a.vc) + (size_t)h * HD * a.cap;
+    const KV *kc = reinterpret_cast<const KV *>(a.kc) + (size_t)h * a.cap * HD;
+    const KV *vc = reinterpret_cast<const KV *>(a.vc) + (size_t)h * HD * a.cap;
     // split partials (device-coherent 16-byte stores and loads)
     const __amdgpu_buffer_rsrc_t po = __builtin_amdgcn_make_buffer_rsrc(a.part_o, (short)0, 0x7fffffff, 0x00020000);
 
-    __shared__ u32x4 sm_q[QT][NC * 2 * 64];  // per query tile: [k-step][hi/lo][lane] B operands
+    // B operands per query tile: [k-step][hi/lo][lane], fp32: [16 dims][lane]
+    __shared__ u32x4 sm_q[QT][NC * 2 * 64];
     __shared__ float sm_m[NW][16], sm_l[NW][16];
     __shared__ __align__(16) float sm_o[NW][16][HD + 4];
 
     struct Tile {
-        u32x4 ka[NC], kb[NC], v[ND];
+        u32x4 ka[NC], kb[NC], v[ND];  // fp32: dims 16 c .. of the key in ka[c] (c < NC), kb[c - NC]
     };
     // keys and values are read once per step: non-temporal loads
     auto load = [&](int t, Tile &T) {
-        const int k0 = kbeg + 32 * t;
+        const int k0 = kbeg + TK * t;
+        if constexpr (F32) {
+            const KV *kp = kc + (size_t)min(k0 + n, kend - 1) * HD + 4 * g;
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                T.ka[c] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(kp + 16 * c));
+                T.kb[c] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(kp + 16 * (NC + c)));
+            }
+#pragma unroll
+            for (int dt = 0; dt < ND; ++dt)
+                T.v[dt] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(
+                    vc + ((size_t)(k0 >> 5) * HD + dt * 16 + n) * 32 + (k0 & 31) + 4 * g));
+            return;
+        }
         const int ka = min(k0 + 8 * (n >> 2) + (n & 3), kend - 1);
         const int kb = min(k0 + 8 * (n >> 2) + 4 + (n & 3), kend - 1);
 #pragma unroll
@@ -1113,6 +1286,16 @@ __global__ __launch_bounds__(64 * NW) void k_attn_mfma(AttnArgs a)
     for (int qt = 0; qt < QT; ++qt) {
         const int tok = 16 * qt + n;
         anc[qt] = tok < M ? a.tm.anc[tok] : 0ull;
+        if constexpr (F32) {
+            // 4 dims of query row (e / 4) % 16 per thread and pass
+            for (int e = threadIdx.x; e < 4 * HD; e += 64 * NW) {
+                const int qr = (e >> 2) & 15, qc = e >> 6, qg = e & 3, row = 16 * qt + qr;
+                float4 x0 = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (row < M) x0 = *reinterpret_cast<const float4 *>(a.q + (size_t)row * D + h * HD + qc * 16 + qg * 4);
+                sm_q[qt][qc * 64 + 16 * qg + qr] = __builtin_bit_cast(u32x4, x0);
+            }
+            continue;
+        }
         // thread e < 2*HD converts 8 dims (c, group qg) of query row qr
         const int e = threadIdx.x;
         const int qr = e / (2 * NC * 2) % 16, qc = (e >> 2) % NC, qg = e & 3;
@@ -1142,7 +1325,75 @@ __global__ __launch_bounds__(64 * NW) void k_attn_mfma(AttnArgs a)
         for (int dt = 0; dt < ND; ++dt) o[qt][dt] = (f32x4){0.f, 0.f, 0.f, 0.f};
     }
 
+    // one key tile with 16 keys (fp32 cache): see above
+    auto process_f32 = [&](int t, Tile &cur) {
+        const int k0 = kbeg + TK * t;
+        if (k0 + TK > kend) {
+            // ragged last tile: values of slots past the split end are dropped
+#pragma unroll
+            for (int dt = 0; dt < ND; ++dt)
+#pragma unroll
+                for (int w = 0; w < 4; ++w)
+                    if (k0 + 4 * g + w >= kend) cur.v[dt][w] = 0u;
+        }
+#pragma unroll
+        for (int qt = 0; qt < QT; ++qt) {
+            if (16 * qt >= M) break;
+            f32x4 sa = (f32x4){0.f, 0.f, 0.f, 0.f}, sb = sa;
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                const f32x4 ka = __builtin_bit_cast(f32x4, cur.ka[c]), kb = __builtin_bit_cast(f32x4, cur.kb[c]);
+                const f32x4 qa = __builtin_bit_cast(f32x4, sm_q[qt][c * 64 + lane]);
+                const f32x4 qb = __builtin_bit_cast(f32x4, sm_q[qt][(NC + c) * 64 + lane]);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    sa = __builtin_amdgcn_mfma_f32_16x16x4f32(ka[i], qa[i], sa, 0, 0, 0);
+                    sb = __builtin_amdgcn_mfma_f32_16x16x4f32(kb[i], qb[i], sb, 0, 0, 0);
+                }
+            }
+            // scores of query n for keys k0 + 4 g + i
+            float sv[4], mt = -INFINITY;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int key = k0 + 4 * g + i, sh = key - P;
+                const bool vis = key < kend && (sh < 0 || ((anc[qt] >> (sh & 63)) & 1ull));
+                sv[i] = vis ? (sa[i] + sb[i]) * scale2 : -INFINITY;
+                mt = fmaxf(mt, sv[i]);
+            }
+            mt = fmaxf(mt, __shfl_xor(mt, 16));
+            mt = fmaxf(mt, __shfl_xor(mt, 32));
+            const float mnew = fmaxf(m_run[qt], mt);
+            const float alpha = m_run[qt] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run[qt] - mnew);
+            float ps = 0.f, pv[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                pv[i] = sv[i] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(sv[i] - mnew);
+                ps += pv[i];
+            }
+            ps += __shfl_xor(ps, 16);
+            ps += __shfl_xor(ps, 32);
+            l_run[qt] = l_run[qt] * alpha + ps;
+            m_run[qt] = mnew;
+            float al[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) al[j] = __shfl(alpha, 4 * g + j);
+#pragma unroll
+            for (int dt = 0; dt < ND; ++dt)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) o[qt][dt][j] *= al[j];
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int dt = 0; dt < ND; ++dt)
+                    o[qt][dt] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                        pv[j], __builtin_bit_cast(f32x4, cur.v[dt])[j], o[qt][dt], 0, 0, 0);
+        }
+    };
     auto process = [&](int t, Tile &cur) {
+        if constexpr (F32) {
+            process_f32(t, cur);
+            return;
+        }
         const int k0 = kbeg + 32 * t;
         if (k0 + 32 > kend) {
             // ragged last tile: values of slots past the split end are dropped
@@ -1353,174 +1604,6 @@ __global__ __launch_bounds__(64 * NW) void k_attn_mfma(AttnArgs a)
         }
     }
     if (threadIdx.x == 0) __hip_atomic_store(a.cnt + h, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// fp32 cache (VALU).  K/V tiles of 32 keys sit in LDS as fp32; 16 queries
-// at a time; an online softmax keeps (max, sum, o) per query.
-
-template <int HD>
-__global__ __launch_bounds__(256) void k_attn_f32(AttnArgs a)
-{
-    constexpr int DPT = HD / 16;  // output dims per thread
-    const int split = blockIdx.x, h = blockIdx.y, tid = threadIdx.x;
-    const int M = a.tm.M, P = a.tm.P, total = P + M;
-    const int kb = split * a.keys_per_split;
-    const int ke = min(total, kb + a.keys_per_split);
-    const float scale = 1.0f / sqrtf((float)HD);
-    const float *kc = reinterpret_cast<const float *>(a.kc) + (size_t)h * a.cap * HD;
-    const float *vc = reinterpret_cast<const float *>(a.vc) + (size_t)h * HD * a.cap;
-    const int D = a.H * HD;
-
-    __shared__ float qs[16][HD];
-    __shared__ float kt[DV_ATTN_TILE][HD + 1];
-    __shared__ float vt[DV_ATTN_TILE][HD + 1];
-    __shared__ float sc[16][DV_ATTN_TILE + 1];
-    __shared__ float mrun[16], lrun[16], alph[16];
-
-    const int qi = tid >> 4, dd = (tid & 15) * DPT;
-    for (int q0 = 0; q0 < M; q0 += 16) {
-        const int nq = min(16, M - q0);
-        for (int e = tid; e < 16 * HD; e += 256) {
-            const int i = e / HD, d = e % HD;
-            qs[i][d] = i < nq ? a.q[(size_t)(q0 + i) * D + h * HD + d] : 0.f;
-        }
-        if (tid < 16) { mrun[tid] = -INFINITY; lrun[tid] = 0.f; }
-        float o[DPT];
-#pragma unroll
-        for (int c = 0; c < DPT; ++c) o[c] = 0.f;
-        __syncthreads();
-
-        for (int t0 = kb; t0 < ke; t0 += DV_ATTN_TILE) {
-            const int nk = min(DV_ATTN_TILE, ke - t0);
-            for (int e = tid; e < DV_ATTN_TILE * HD; e += 256) {
-                const int j = e / HD, d = e % HD;
-                kt[j][d] = j < nk ? kc[(size_t)(t0 + j) * HD + d] : 0.f;
-                const int jv = e % DV_ATTN_TILE, dv = e / DV_ATTN_TILE;
-                vt[jv][dv] = jv < nk ? vc[v_index(dv, t0 + jv, HD)] : 0.f;
-            }
-            __syncthreads();
-            for (int e = tid; e < 16 * DV_ATTN_TILE; e += 256) {
-                const int i = e / DV_ATTN_TILE, j = e % DV_ATTN_TILE;
-                const int key = t0 + j;
-                bool vis = i < nq && j < nk;
-                if (vis && key >= P) vis = (a.tm.anc[q0 + i] >> (key - P)) & 1ull;
-                float s = -INFINITY;
-                if (vis) {
-                    float acc = 0.f;
-#pragma unroll 8
-                    for (int d = 0; d < HD; ++d) acc = fmaf(qs[i][d], kt[j][d], acc);
-                    s = acc * scale;
-                }
-                sc[i][j] = s;
-            }
-            __syncthreads();
-            if (tid < 16) {
-                float mx = -INFINITY;
-                for (int j = 0; j < DV_ATTN_TILE; ++j) mx = fmaxf(mx, sc[tid][j]);
-                const float mold = mrun[tid];
-                const float mnew = fmaxf(mold, mx);
-                float al = 1.f, sum = 0.f;
-                if (mnew != -INFINITY) {
-                    al = (mold == -INFINITY) ? 0.f : expf(mold - mnew);
-                    for (int j = 0; j < DV_ATTN_TILE; ++j) {
-                        const float sj = sc[tid][j];
-                        const float p = (sj == -INFINITY) ? 0.f : expf(sj - mnew);
-                        sc[tid][j] = p;
-                        sum += p;
-                    }
-                } else {
-                    for (int j = 0; j < DV_ATTN_TILE; ++j) sc[tid][j] = 0.f;
-                }
-                lrun[tid] = lrun[tid] * al + sum;
-                mrun[tid] = mnew;
-                alph[tid] = al;
-            }
-            __syncthreads();
-            {
-                const float al = alph[qi];
-#pragma unroll
-                for (int c = 0; c < DPT; ++c) {
-                    float acc = o[c] * al;
-                    for (int j = 0; j < DV_ATTN_TILE; ++j) acc = fmaf(sc[qi][j], vt[j][dd + c], acc);
-                    o[c] = acc;
-                }
-            }
-            __syncthreads();
-        }
-        if (a.n_split == 1) {
-            if (q0 + qi < (a.out_split ? split_rows(a.tm.Mpad, a.tm.half) : a.tm.Mpad)) {
-#pragma unroll
-                for (int c = 0; c < DPT; ++c) {
-                    const float r = qi < nq ? o[c] / lrun[qi] : 0.f;
-                    if (a.out_split)
-                        store_split(a.out_split, q0 + qi, h * HD + dd + c, split_mt(a.tm.Mpad, a.tm.half), r);
-                    else a.out[(size_t)(q0 + qi) * D + h * HD + dd + c] = r;
-                }
-            }
-        } else {
-            const size_t pbase = ((size_t)h * a.n_split + split) * DV_TREE_MAX;
-            if (qi < nq) {
-#pragma unroll
-                for (int c = 0; c < DPT; ++c) a.part_o[(pbase + q0 + qi) * HD + dd + c] = o[c];
-            }
-            if (tid < nq) {
-                a.part_m[pbase + q0 + tid] = mrun[tid];
-                a.part_l[pbase + q0 + tid] = lrun[tid];
-            }
-        }
-        __syncthreads();
-    }
-}
-
-// Combine the splits of each (node, head): softmax-weighted sum of the split
-// outputs.  Splits are read 16 at a time (all loads of a chunk in flight
-// together) and folded in split order with a running maximum.  Grid (Mpad, H),
-// block hd threads; rows >= M are 0.
-__global__ __launch_bounds__(128) void k_attn_merge(AttnArgs a)
-{
-    constexpr int CH = 16;
-    const int i = blockIdx.x, h = blockIdx.y, d = threadIdx.x, HD = a.hd;
-    const int M = a.tm.M, MT = split_mt(gridDim.x, a.tm.half);
-    if (i >= M) {
-        if (a.out_split) {
-            if (i < split_rows(gridDim.x, a.tm.half)) store_split(a.out_split, i, h * HD + d, MT, 0.f);
-        }
-        else {
-            a.out[(size_t)i * a.H * HD + h * HD + d] = 0.f;
-        }
-        return;
-    }
-    const size_t base = (size_t)h * a.n_split * DV_TREE_MAX + i;
-    float run_m = -INFINITY, l = 0.f, o = 0.f;
-    for (int s0 = 0; s0 < a.n_split; s0 += CH) {
-        float ms[CH], ls[CH], os[CH];
-#pragma unroll
-        for (int c = 0; c < CH; ++c) {
-            const size_t ps = base + (size_t)min(s0 + c, a.n_split - 1) * DV_TREE_MAX;
-            ms[c] = a.part_m[ps];
-            ls[c] = a.part_l[ps];
-            os[c] = a.part_o[ps * HD + d];
-        }
-        float mx = run_m;
-#pragma unroll
-        for (int c = 0; c < CH; ++c)
-            if (s0 + c < a.n_split) mx = fmaxf(mx, ms[c]);
-        if (mx == -INFINITY) continue;
-        const float sc = run_m == -INFINITY ? 0.f : expf(run_m - mx);
-        l *= sc;
-        o *= sc;
-#pragma unroll
-        for (int c = 0; c < CH; ++c) {
-            if (s0 + c < a.n_split && ms[c] != -INFINITY) {
-                const float w = expf(ms[c] - mx);
-                l = fmaf(w, ls[c], l);
-                o = fmaf(w, os[c], o);
-            }
-        }
-        run_m = mx;
-    }
-    if (a.out_split) store_split(a.out_split, i, h * HD + d, MT, o / l);
-    else a.out[(size_t)i * a.H * HD + h * HD + d] = o / l;
 }
 
 // ---------------------------------------------------------------------------
@@ -2467,6 +2550,21 @@ static const void *proj_kernel_mt(int mt)
     }
 }
 
+// fp32 weights: 4 waves; the half split layout does not exist here, so mt 0
+// (at most 8 nodes) runs as one token tile
+template <int EPI, int RB>
+static const void *proj_f32_mt(int mt)
+{
+    switch (mt) {
+    case 0:
+    case 1: return (const void *)k_proj_f32<1, EPI, 4, 4, RB>;
+    case 2: return (const void *)k_proj_f32<2, EPI, 4, 4, RB>;
+    case 3: return (const void *)k_proj_f32<3, EPI, 4, 4, RB>;
+    case 4: return (const void *)k_proj_f32<4, EPI, 4, 4, RB>;
+    default: return nullptr;
+    }
+}
+
 template <int EPI>
 static const void *gemm_kernel(int wkind, int use_mfma, int mt, int rb)
 {
@@ -2489,9 +2587,11 @@ static const void *gemm_kernel(int wkind, int use_mfma, int mt, int rb)
             if (rb == 2) return q8 ? proj_kernel_mt<EPI, uint16_t, 2, true>(mt) : proj_kernel_mt<EPI, uint16_t, 2, false>(mt);
             return nullptr;
         }
-        if (wkind == W_BF16) return (const void *)k_gemm_valu<uint16_t, EPI, uint16_t>;
-        if (wkind == W_F32) return (const void *)k_gemm_valu<float, EPI, float>;
-        return nullptr;  // int8 weights have no VALU kernel
+        if constexpr (EPI == EPI_RESID) {
+            if (wkind == W_BF16) return (const void *)k_gemm_valu;
+        }
+        if (wkind == W_F32) return rb == 4 ? proj_f32_mt<EPI, 4>(mt) : (rb == 2 ? proj_f32_mt<EPI, 2>(mt) : nullptr);
+        return nullptr;
     }
 }
 
@@ -2557,6 +2657,9 @@ hipError_t launch_pack(const GemmArgs &a, int epi, int wkind, void *dst, hipStre
     } else if (wkind == W_BF16) {
         hipLaunchKernelGGL(k_pack_blocks, dim3(a.n_groups * a.rb, std::min(a.K / 32, 64)), dim3(64), 0, s, a, epi,
                            static_cast<uint16_t *>(dst));
+    } else if (wkind == W_F32) {
+        hipLaunchKernelGGL(k_pack_blocks_f32, dim3(a.n_groups * a.rb, std::min(a.K / 16, 64)), dim3(64), 0, s, a, epi,
+                           static_cast<float *>(dst));
     } else {
         return hipErrorInvalidValue;
     }
@@ -2589,54 +2692,39 @@ hipError_t launch_embed_norm(const NormArgs &a, int Mpad, int weight_bf16, hipSt
     return weight_bf16 ? embed_norm_dispatch<uint16_t>(a, Mpad, s) : embed_norm_dispatch<float>(a, Mpad, s);
 }
 
-hipError_t launch_attention(const AttnArgs &a, int kv_bf16, hipStream_t s)
+// QT query tiles: every key tile serves all of them, with the per-tile outputs
+// in registers.  A split of at most 8 key tiles runs 8 waves holding one tile
+// each, a longer one 4 waves with two tiles in flight each (one query tile) or
+// one each (more: the outputs take the registers).
+template <int HD, int QT, typename KV>
+static void attention_qt(const AttnArgs &a, hipStream_t s)
 {
-    const dim3 grid(a.n_split, a.H), block(256);
-    // up to 8 key tiles per split: 8 waves holding one tile each; longer
-    // splits: 4 waves with two tiles in flight each (one query tile) or one
-    // each (more)
-    const bool short_split = a.keys_per_split <= 8 * DV_ATTN_TILE;
-    const dim3 b8(512), b4(256);
-    // more than 16 nodes: every key tile serves all query tiles, with the
-    // per-tile outputs in registers
-    const int qt = a.tm.Mpad / 16;
-    if (qt < 1 || qt > 4) return hipErrorInvalidValue;
-    if (!kv_bf16) {
-        if (a.hd == 128) hipLaunchKernelGGL(k_attn_f32<128>, grid, block, 0, s, a);
-        else if (a.hd == 64) hipLaunchKernelGGL(k_attn_f32<64>, grid, block, 0, s, a);
-        else return hipErrorInvalidValue;
-        return hipGetLastError();
-    }
-    if (a.hd == 128) {
-        if (short_split) {
-            if (qt == 1) hipLaunchKernelGGL((k_attn_mfma<128, 8, false, 1>), grid, b8, 0, s, a);
-            else if (qt == 2) hipLaunchKernelGGL((k_attn_mfma<128, 8, false, 2>), grid, b8, 0, s, a);
-            else if (qt == 3) hipLaunchKernelGGL((k_attn_mfma<128, 8, false, 3>), grid, b8, 0, s, a);
-            else hipLaunchKernelGGL((k_attn_mfma<128, 8, false, 4>), grid, b8, 0, s, a);
-        } else if (qt == 1) hipLaunchKernelGGL((k_attn_mfma<128, 4, true, 1>), grid, b4, 0, s, a);
-        else if (qt == 2) hipLaunchKernelGGL((k_attn_mfma<128, 4, false, 2>), grid, b4, 0, s, a);
-        else if (qt == 3) hipLaunchKernelGGL((k_attn_mfma<128, 4, false, 3>), grid, b4, 0, s, a);
-        else hipLaunchKernelGGL((k_attn_mfma<128, 4, false, 4>), grid, b4, 0, s, a);
-    } else if (a.hd == 64) {
-        if (short_split) {
-            if (qt == 1) hipLaunchKernelGGL((k_attn_mfma<64, 8, false, 1>), grid, b8, 0, s, a);
-            else if (qt == 2) hipLaunchKernelGGL((k_attn_mfma<64, 8, false, 2>), grid, b8, 0, s, a);
-            else if (qt == 3) hipLaunchKernelGGL((k_attn_mfma<64, 8, false, 3>), grid, b8, 0, s, a);
-            else hipLaunchKernelGGL((k_attn_mfma<64, 8, false, 4>), grid, b8, 0, s, a);
-        } else if (qt == 1) hipLaunchKernelGGL((k_attn_mfma<64, 4, true, 1>), grid, b4, 0, s, a);
-        else if (qt == 2) hipLaunchKernelGGL((k_attn_mfma<64, 4, false, 2>), grid, b4, 0, s, a);
-        else if (qt == 3) hipLaunchKernelGGL((k_attn_mfma<64, 4, false, 3>), grid, b4, 0, s, a);
-        else hipLaunchKernelGGL((k_attn_mfma<64, 4, false, 4>), grid, b4, 0, s, a);
-    } else {
-        return hipErrorInvalidValue;
+    constexpr int TK = sizeof(KV) == 4 ? 16 : 32;
+    const dim3 grid(a.n_split, a.H);
+    if (a.keys_per_split <= 8 * TK)
+        hipLaunchKernelGGL((k_attn_mfma<HD, 8, false, QT, KV>), grid, dim3(512), 0, s, a);
+    else
+        hipLaunchKernelGGL((k_attn_mfma<HD, 4, QT == 1, QT, KV>), grid, dim3(256), 0, s, a);
+}
+
+template <int HD, typename KV>
+static hipError_t attention_hd(const AttnArgs &a, hipStream_t s)
+{
+    switch (a.tm.Mpad / 16) {
+    case 1: attention_qt<HD, 1, KV>(a, s); break;
+    case 2: attention_qt<HD, 2, KV>(a, s); break;
+    case 3: attention_qt<HD, 3, KV>(a, s); break;
+    case 4: attention_qt<HD, 4, KV>(a, s); break;
+    default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
 
-hipError_t launch_attn_merge(const AttnArgs &a, int Mpad, hipStream_t s)
+hipError_t launch_attention(const AttnArgs &a, int kv_bf16, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_attn_merge, dim3(Mpad, a.H), dim3(a.hd), 0, s, a);
-    return hipGetLastError();
+    if (a.hd == 128) return kv_bf16 ? attention_hd<128, uint16_t>(a, s) : attention_hd<128, float>(a, s);
+    if (a.hd == 64) return kv_bf16 ? attention_hd<64, uint16_t>(a, s) : attention_hd<64, float>(a, s);
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_accept(const AcceptArgs &a, hipStream_t s)
