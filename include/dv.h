@@ -280,8 +280,8 @@ int dv_kv_commit(dv_handle *h, dv_kv *kv, const dv_accept *accept);
 /* Build the cache from a prompt (the target's prefill before the first
  * draft round, Section 3.1; the Limitations section names long-context
  * prefill as the method's bottleneck): appends the K/V of tokens[0..n) after the kv->len
- * committed entries and commits all of them (kv->len += n).  With bf16
- * weights and n > max_tree the prompt runs as causal chunks of up to 1024
+ * committed entries and commits all of them (kv->len += n).  With bf16 or
+ * int8 weights and n > max_tree the prompt runs as causal chunks of up to 1024
  * tokens (an MFMA GEMM with fused epilogues for the projections, a causal
  * attention kernel);
  * otherwise as chains of at most max_tree tokens through the verify step's

@@ -2,16 +2,17 @@
 import os
 import shutil
 import subprocess
+import tempfile
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libdv.so")
-SOURCES = ["dv_kernels.hip", "dv_engine.cpp"]
+SOURCES = ["dv_kernels.hip", "dv_prefill.hip", "dv_engine.cpp"]
 
 HIPCC_FLAGS = [
-    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
+    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     # packed fp32 VALU ops stay off in every HIP build of this library
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-function",
@@ -26,16 +27,24 @@ def hipcc() -> str:
 
 
 def build(verbose: bool = False) -> str:
-    """Always recompiles; writes libdv.so atomically next to this file."""
-    tmp = LIB + ".tmp%d" % os.getpid()
-    cmd = [hipcc()] + HIPCC_FLAGS + ["-I", INCLUDE, "-I", CSRC] + \
-        [os.path.join(CSRC, s) for s in SOURCES] + ["-o", tmp]
-    res = subprocess.run(cmd, capture_output=True, text=True)
-    if res.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + res.stdout + res.stderr)
+    """Always recompiles (the sources in parallel); writes libdv.so atomically
+    next to this file."""
+    with tempfile.TemporaryDirectory() as tmp:
+        base = [hipcc()] + HIPCC_FLAGS + ["-I", INCLUDE, "-I", CSRC]
+        objs = [os.path.join(tmp, s + ".o") for s in SOURCES]
+        jobs = [subprocess.Popen(base + ["-c", os.path.join(CSRC, s), "-o", o], stdout=subprocess.PIPE,
+                                 stderr=subprocess.STDOUT, text=True) for s, o in zip(SOURCES, objs)]
+        logs = [j.communicate()[0] for j in jobs]
+        if any(j.returncode for j in jobs):
+            raise RuntimeError("hipcc failed:\n" + "".join(logs))
+        out = LIB + ".tmp%d" % os.getpid()
+        res = subprocess.run([hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC"] + objs + ["-o", out],
+                             capture_output=True, text=True)
+        if res.returncode != 0:
+            raise RuntimeError("hipcc failed:\n" + res.stdout + res.stderr)
     if verbose:
-        print(res.stderr)
-    os.replace(tmp, LIB)
+        print("".join(logs) + res.stderr)
+    os.replace(out, LIB)
     return LIB
 
 

@@ -72,13 +72,17 @@ struct dv_handle {
     DevAccept *d_acc = nullptr, *h_acc = nullptr;
     float *logits_ws = nullptr;  // [max_tree][vocab] logits of a sampled step without out_logits
     // large-M prefill (allocated at its first use, sized for pf_cap tokens,
-    // a multiple of 128): residual stream, rotated queries, the split-layout
+    // a multiple of 128; pf_part and pf_cnt for the split-K units of any
+    // chunk): residual stream, rotated queries, the split-layout
     // operands (norm numerators, attention output, SwiGLU output) and the
     // norms' sums of squares over 64-row slices
     int pf_cap = 0;
+    void *pf_block = nullptr;  // the allocation that holds them all
     int32_t *pf_tok = nullptr;
     float *pf_x = nullptr, *pf_q = nullptr, *pf_ssq = nullptr;
     uint16_t *pf_us = nullptr, *pf_as = nullptr, *pf_hs = nullptr;
+    float *pf_part = nullptr;
+    uint32_t *pf_cnt = nullptr;
     // draft side
     bool draft = false;
     const void *dgf_h = nullptr, *dgf_e = nullptr, *dgf_g = nullptr;  // W_h, W_e [d][d], W_g [d][2d]
@@ -492,38 +496,60 @@ int prepare_sampled(dv_handle *h, const int32_t *tokens, const int32_t *parents,
 
 // Large-M prefill: chunks of up to DV_PF_CHUNK tokens, each one causal pass
 // through all layers on the prefill GEMM (k_pf_gemm, fused epilogues) and
-// the causal attention kernel; bf16 weights whose projections use the packed
-// block order.
+// the causal attention kernel; bf16 and int8 weights whose projections use the
+// packed block order.
 constexpr int DV_PF_CHUNK = 1024;
 
 bool pf_supported(const dv_handle *h)
 {
     const dv_config &c = h->cfg;
-    return h->wkind == W_BF16 && h->p_qkv.mfma && h->p_o.mfma && h->p_gu.mfma && h->p_down.mfma &&
+    return h->wkind != W_F32 && h->p_qkv.mfma && h->p_o.mfma && h->p_gu.mfma && h->p_down.mfma &&
            c.d_model % 64 == 0 && (c.head_dim == 64 || c.head_dim == 128);
 }
 
-int pf_reserve(dv_handle *h, int tokens)
+// The workspace is one allocation (a new handle's first prefill pays for it),
+// with the split-K part only where prefills run (the draft needs the rows
+// only).  Nothing but the counters has to start at zero: rows past the chunk's
+// tokens are computed with, but every token's column stays its own and theirs
+// are dropped.
+int pf_reserve(dv_handle *h, int tokens, bool split)
 {
-    const int cap = round_up(std::max(tokens, 1), 128);
-    if (h->pf_cap >= cap) return DV_OK;
+    const int cap = std::max(round_up(std::max(tokens, 1), 128), h->pf_cap);
+    if (h->pf_cap >= cap && (h->pf_part || !split)) return DV_OK;
+    split = split || h->pf_part;
     const dv_config &c = h->cfg;
-    for (void *p : {(void *)h->pf_tok, (void *)h->pf_x, (void *)h->pf_q, (void *)h->pf_ssq, (void *)h->pf_us,
-                    (void *)h->pf_as, (void *)h->pf_hs})
-        if (p) (void)hipFree(p);
-    h->pf_tok = nullptr;
-    h->pf_x = h->pf_q = h->pf_ssq = nullptr;
-    h->pf_us = h->pf_as = h->pf_hs = nullptr;
+    if (h->pf_block) (void)hipFree(h->pf_block);
+    h->pf_block = nullptr;
+    h->pf_part = nullptr;
     h->pf_cap = 0;
     const size_t Mc = cap, d = c.d_model, F = std::max(c.d_ffn, 1);
-    auto dalloc = [&](void **p, size_t bytes) -> bool {
-        return hipMalloc(p, bytes) == hipSuccess && hipMemset(*p, 0, bytes) == hipSuccess;
+    const size_t cnt_bytes = DV_PF_MAX_TILES * 4;
+    size_t total = 0;
+    auto take = [&](size_t bytes) {
+        const size_t at = total;
+        total += (bytes + 255) / 256 * 256;
+        return at;
     };
-    const bool ok = dalloc((void **)&h->pf_tok, Mc * 4) && dalloc((void **)&h->pf_x, Mc * d * 4) &&
-                    dalloc((void **)&h->pf_q, Mc * d * 4) && dalloc((void **)&h->pf_ssq, Mc * (d / 64 + 1) * 4) &&
-                    dalloc((void **)&h->pf_us, Mc * d * 4) && dalloc((void **)&h->pf_as, Mc * d * 4) &&
-                    dalloc((void **)&h->pf_hs, Mc * F * 4);
-    if (!ok) return set_err(h, DV_ENOMEM, "prefill workspace for %d tokens: allocation failed", tokens);
+    const size_t o_tok = take(Mc * 4), o_x = take(Mc * d * 4), o_q = take(Mc * d * 4), o_ssq = take(Mc * (d / 64 + 1) * 4),
+                 o_us = take(Mc * d * 4), o_as = take(Mc * d * 4), o_hs = take(Mc * F * 4),
+                 o_cnt = take(split ? cnt_bytes : 0), o_part = take(split ? (size_t)DV_PF_PART_TILES * 1024 : 0);
+    char *b = nullptr;
+    if (hipMalloc((void **)&b, total) != hipSuccess)
+        return set_err(h, DV_ENOMEM, "prefill workspace for %d tokens: allocation failed", tokens);
+    if (split && hipMemset(b + o_cnt, 0, cnt_bytes) != hipSuccess) {
+        (void)hipFree(b);
+        return set_err(h, DV_ENOMEM, "prefill workspace for %d tokens: clearing failed", tokens);
+    }
+    h->pf_block = b;
+    h->pf_tok = (int32_t *)(b + o_tok);
+    h->pf_x = (float *)(b + o_x);
+    h->pf_q = (float *)(b + o_q);
+    h->pf_ssq = (float *)(b + o_ssq);
+    h->pf_us = (uint16_t *)(b + o_us);
+    h->pf_as = (uint16_t *)(b + o_as);
+    h->pf_hs = (uint16_t *)(b + o_hs);
+    h->pf_cnt = split ? (uint32_t *)(b + o_cnt) : nullptr;
+    h->pf_part = split ? (float *)(b + o_part) : nullptr;
     h->pf_cap = cap;
     return DV_OK;
 }
@@ -533,13 +559,15 @@ int prefill_large(dv_handle *h, const int32_t *tokens, int n, dv_kv *kv, int32_t
     const dv_config &c = h->cfg;
     const int d = c.d_model, F = c.d_ffn, H = c.n_heads, hd = c.head_dim;
     hipStream_t s = h->stream;
-    int rc = pf_reserve(h, std::min(n, DV_PF_CHUNK));
+    int rc = pf_reserve(h, std::min(n, DV_PF_CHUNK), true);
     if (rc) return rc;
     auto ck = [&](hipError_t e, const char *what) -> int { return e == hipSuccess ? DV_OK : hip_fail(h, e, what); };
     const size_t layer_kv = (size_t)H * kv->capacity * hd;
+    const bool q8 = h->wkind == W_I8;
     int done = 0;
     while (done < n) {
-        const int M = std::min(DV_PF_CHUNK, n - done), Mp = round_up(M, 128), P0 = kv->len;
+        const int M = std::min(DV_PF_CHUNK, n - done), MT = std::max(ceil_div(M, 16), DV_PF_MIN_TILES), Mp = 16 * MT;
+        const int P0 = kv->len;
         HIPCHK(h, hipMemcpyAsync(h->pf_tok, tokens + done, (size_t)M * 4, hipMemcpyHostToDevice, s));
         prof_begin(h, DV_K_NORM);
         rc = ck(launch_pf_embed(h->pf_tok, h->embed, M, Mp, d, h->layers[0].attn_norm, h->pf_x, h->pf_us, h->pf_ssq,
@@ -548,7 +576,9 @@ int prefill_large(dv_handle *h, const int32_t *tokens, int n, dv_kv *kv, int32_t
         prof_end(h);
         if (rc) return rc;
         PfArgs base{};
-        base.MT = Mp / 16;
+        base.MT = MT;
+        base.part = h->pf_part;
+        base.cnt = h->pf_cnt;
         base.M = M;
         base.P0 = P0;
         base.ssq_in = h->pf_ssq;
@@ -564,15 +594,22 @@ int prefill_large(dv_handle *h, const int32_t *tokens, int n, dv_kv *kv, int32_t
         base.x = h->pf_x;
         base.us = h->pf_us;
         base.ssq_out = h->pf_ssq;
-        auto gemm = [&](int epi, const uint16_t *packed, int rows, int K, const uint16_t *xs, const void *gain) -> int {
+        const PfPlan plan_qkv = pf_plan(3 * d / 16, MT, d, q8, q8 ? 2 : 1, h->n_cu),
+                     plan_o = pf_plan(d / 16, MT, d, q8, 1, h->n_cu), plan_gu = pf_plan(F / 8, MT, d, q8, 1, h->n_cu),
+                     plan_down = pf_plan(d / 16, MT, F, q8, 1, h->n_cu);
+        auto gemm = [&](const PfPlan &p, int epi, const uint16_t *packed, const float *scale, int rows, int K,
+                        const uint16_t *xs, const void *gain) -> int {
             PfArgs a = base;
             a.packed = packed;
+            a.scale = scale;
             a.NB = rows / 16;
             a.K = K;
             a.xs = xs;
+            a.n_tt = p.n_tt;
+            a.ks = p.ks;
             a.gain = static_cast<const uint16_t *>(gain);
             prof_begin(h, DV_K_GEMM);
-            const hipError_t e = launch_pf_gemm(a, epi, s);
+            const hipError_t e = launch_pf_gemm(a, p, epi, s);
             prof_end(h);
             return ck(e, "prefill GEMM");
         };
@@ -580,16 +617,16 @@ int prefill_large(dv_handle *h, const int32_t *tokens, int n, dv_kv *kv, int32_t
             const LayerW &w = h->layers[l];
             base.kc = static_cast<uint16_t *>(kv->k) + (size_t)l * layer_kv;
             base.vc = static_cast<uint16_t *>(kv->v) + (size_t)l * layer_kv;
-            if ((rc = gemm(EPI_QKV, w.pk_qkv, 3 * d, d, h->pf_us, nullptr))) return rc;
+            if ((rc = gemm(plan_qkv, EPI_QKV, w.pk_qkv, w.ps_qkv, 3 * d, d, h->pf_us, nullptr))) return rc;
             prof_begin(h, DV_K_ATTN);
-            rc = ck(launch_attn_causal(h->pf_q, base.kc, base.vc, M, P0, H, hd, kv->capacity, Mp / 16, h->pf_as, s),
+            rc = ck(launch_attn_causal(h->pf_q, base.kc, base.vc, M, P0, H, hd, kv->capacity, MT, h->pf_as, s),
                     "causal attention");
             prof_end(h);
             if (rc) return rc;
-            if ((rc = gemm(EPI_RESID, w.pk_o, d, d, h->pf_as, w.ffn_norm))) return rc;
-            if ((rc = gemm(EPI_SWIGLU, w.pk_gu, 2 * F, d, h->pf_us, nullptr))) return rc;
+            if ((rc = gemm(plan_o, EPI_RESID, w.pk_o, w.ps_o, d, d, h->pf_as, w.ffn_norm))) return rc;
+            if ((rc = gemm(plan_gu, EPI_SWIGLU, w.pk_gu, w.ps_gu, 2 * F, d, h->pf_us, nullptr))) return rc;
             const void *next_gain = l + 1 < c.n_layers ? h->layers[l + 1].attn_norm : h->final_norm;
-            if ((rc = gemm(EPI_RESID, w.pk_down, d, F, h->pf_hs, next_gain))) return rc;
+            if ((rc = gemm(plan_down, EPI_RESID, w.pk_down, w.ps_down, d, F, h->pf_hs, next_gain))) return rc;
         }
         const bool last = done + M == n;
         if (last) {
@@ -609,15 +646,17 @@ int prefill_large(dv_handle *h, const int32_t *tokens, int n, dv_kv *kv, int32_t
             rc = ck(launch_embed_norm(na, 16, 1, s), "prefill final norm");
             prof_end(h);
             if (rc) return rc;
+            const GemmPlan lm = step_plan(h->p_lm, EPI_LOGITS, h->wkind, 0, h->n_cu);
             GemmArgs g{};
             g.packed = h->pk_lm;
+            g.scale = h->ps_lm;
             g.N = c.vocab;
             g.K = d;
-            g.n_tiles = h->p_lm.n_tiles;
-            g.rb = h->p_lm.rb;
-            g.n_groups = h->p_lm.n_groups;
-            g.ks = h->p_lm.ks;
-            g.n_units = gemm_units(h->p_lm);
+            g.n_tiles = lm.n_tiles;
+            g.rb = lm.rb;
+            g.n_groups = lm.n_groups;
+            g.ks = lm.ks;
+            g.n_units = gemm_units(lm);
             g.xs = h->u_s;
             g.M = 1;
             g.Mpad = 16;
@@ -629,14 +668,14 @@ int prefill_large(dv_handle *h, const int32_t *tokens, int n, dv_kv *kv, int32_t
             g.arg_val = h->arg_val;
             g.arg_idx = h->arg_idx;
             ProfEv *ev = prof_pair(h, DV_K_GEMM);
-            rc = ck(launch_gemm(g, gemm_grid(h->p_lm, EPI_LOGITS, h->wkind, 0, h->n_cu), EPI_LOGITS, h->wkind, 1, s,
+            rc = ck(launch_gemm(g, gemm_grid(lm, EPI_LOGITS, h->wkind, 0, h->n_cu), EPI_LOGITS, h->wkind, 1, s,
                                 ev ? ev->a : nullptr, ev ? ev->b : nullptr),
                     "prefill lm_head");
             if (rc) return rc;
             AcceptArgs ac{};
             ac.arg_val = h->arg_val;
             ac.arg_idx = h->arg_idx;
-            ac.n_parts = h->p_lm.n_groups;
+            ac.n_parts = lm.n_groups;
             ac.M = 1;
             ac.Mpad = 16;
             ac.parents[0] = -1;
@@ -668,7 +707,7 @@ int draft_forward_impl(dv_handle *h, const int32_t *tokens, const int32_t *paren
     const dv_config &c = h->cfg;
     const int d = c.d_model;
     hipStream_t s = h->stream;
-    int rc = pf_reserve(h, std::max(n, 1));
+    int rc = pf_reserve(h, std::max(n, 1), false);
     if (rc) return rc;
     // gated fusion on the weight-streaming projections: h1 = W_h f, h2 = W_e e,
     // z = W_g [h1 || h2], x0 = sigmoid(z) h1 + (1 - sigmoid(z)) h2
@@ -1215,7 +1254,7 @@ int dv_draft_init(const dv_config *cfg, const dv_weights *w, const dv_dgf_weight
               hipMalloc((void **)&h->tk_p, DV_TREE_MAX * DV_TOPK_MAX * 4) == hipSuccess &&
               hipHostMalloc((void **)&h->tk_tok_h, DV_TREE_MAX * DV_TOPK_MAX * 4, hipHostMallocDefault) == hipSuccess &&
               hipHostMalloc((void **)&h->tk_p_h, DV_TREE_MAX * DV_TOPK_MAX * 4, hipHostMallocDefault) == hipSuccess;
-    if (!ok || pf_reserve(h, DV_TREE_MAX) != DV_OK) {
+    if (!ok || pf_reserve(h, DV_TREE_MAX, false) != DV_OK) {
         dv_verify_free(h);
         return set_err(nullptr, DV_ENOMEM, "draft workspace allocation failed");
     }
@@ -1464,9 +1503,7 @@ void dv_verify_free(dv_handle *h)
         if (p) (void)hipFree(p);
     if (h->tk_tok_h) (void)hipHostFree(h->tk_tok_h);
     if (h->tk_p_h) (void)hipHostFree(h->tk_p_h);
-    for (void *p : {(void *)h->pf_tok, (void *)h->pf_x, (void *)h->pf_q, (void *)h->pf_ssq, (void *)h->pf_us,
-                    (void *)h->pf_as, (void *)h->pf_hs})
-        if (p) (void)hipFree(p);
+    if (h->pf_block) (void)hipFree(h->pf_block);
     delete h->h_sd;
     if (h->h_acc) (void)hipHostFree(h->h_acc);
     for (auto &e : h->ev_live) { (void)hipEventDestroy(e.a); (void)hipEventDestroy(e.b); }

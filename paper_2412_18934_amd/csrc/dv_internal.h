@@ -224,15 +224,25 @@ hipError_t launch_accept_sampled(const SampleArgs &a, hipStream_t s);
 // device with hipGetSymbolAddress)
 hipError_t noalloc_scratch(void **out);
 
-// Large-M prefill (bf16 weights, MFMA path): the chunk's activations in split
-// layout of MT = Mp / 16 token tiles (Mp a multiple of 128), norms applied
-// by their consumers from sums of squares over 64-row slices ([Mp][d / 64]).
+// Large-M prefill (bf16 and int8 weights): the chunk's activations in split
+// layout of MT token tiles (Mp = 16 MT rows, at least DV_PF_MIN_TILES tiles),
+// norms applied by their consumers from sums of squares over 64-row slices
+// ([Mp][d / 64]).
+#define DV_PF_MIN_TILES 3
+// 1 KB partial tiles (16 rows x 16 tokens) that the split-K units of one
+// prefill GEMM may write
+#define DV_PF_PART_TILES 65536
+#define DV_PF_MAX_TILES 1024  // split tiles that fit in there (2 or more units of 32 or more)
 struct PfArgs {
     const uint16_t *packed;  // weights in block order
+    const float *scale;      // int8: the row scales in packed row order (null: bf16 weights)
     int NB;                  // 16-row blocks of the matrix
     int K;                   // reduction length (multiple of 32)
     const uint16_t *xs;      // activations, split layout of MT token tiles
     int MT;                  // token tiles of the split layout (Mp / 16)
+    int n_tt, ks;            // token groups and K ranges (PfPlan)
+    float *part;             // ks > 1: the units' partial sums
+    uint32_t *cnt;           // ks > 1: arrivals per tile, 0 between launches
     int M;                   // real tokens (the rest is padding)
     int P0;                  // cache slot / position of token 0
     // input norm (QKV, SWIGLU): rinv = 1/sqrt(sum_j ssq_in[m][j] / d + eps)
@@ -257,8 +267,14 @@ struct PfArgs {
 // embedding rows, the first norm's numerator (split layout) and its sums of squares
 hipError_t launch_pf_embed(const int32_t *tokens, const void *embed, int M, int Mp, int d, const void *gain, float *x,
                            uint16_t *us, float *ssq, hipStream_t s);
+// How a prefill GEMM is cut: workgroup shape (rows per unit and K groups), token
+// tiles per unit (or one less), token groups, K ranges.
+struct PfPlan {
+    int shape, tt, n_tt, ks;
+};
+PfPlan pf_plan(int NB, int MT, int K, bool q8, int min_parts, int n_cu);
 // the prefill GEMM with the EPI_QKV, EPI_SWIGLU or EPI_RESID epilogue
-hipError_t launch_pf_gemm(const PfArgs &a, int epi, hipStream_t s);
+hipError_t launch_pf_gemm(const PfArgs &a, const PfPlan &p, int epi, hipStream_t s);
 // causal attention of the chunk; output in split layout (MT token tiles)
 hipError_t launch_attn_causal(const float *q, const void *kc, const void *vc, int M, int P0, int H, int hd, int cap,
                               int MT, uint16_t *out, hipStream_t s);

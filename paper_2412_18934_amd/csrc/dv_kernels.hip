@@ -25,116 +25,8 @@
 #include <mutex>
 
 #include "dv.h"
+#include "dv_device.h"
 #include "dv_internal.h"
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
-// ---------------------------------------------------------------------------
-// scalar helpers
-
-__device__ __forceinline__ float bf2f(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
-
-// fp32 -> bf16 bits, round to nearest even; NaN stays NaN.
-__device__ __forceinline__ uint16_t f2bf(float f)
-{
-    uint32_t u = __float_as_uint(f);
-    if ((u & 0x7fffffffu) > 0x7f800000u) return 0x7fc0;
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
-}
-
-template <typename T> struct Elem;
-template <> struct Elem<float> {
-    static __device__ __forceinline__ float load(const float *p, size_t i) { return p[i]; }
-    static __device__ __forceinline__ void store(float *p, size_t i, float v) { p[i] = v; }
-};
-template <> struct Elem<uint16_t> {
-    static __device__ __forceinline__ float load(const uint16_t *p, size_t i) { return bf2f(p[i]); }
-    static __device__ __forceinline__ void store(uint16_t *p, size_t i, float v) { p[i] = f2bf(v); }
-};
-
-// Buffer resource over a device allocation (byte offsets below 2 GiB) and the
-// cache-policy bit of buffer instructions for data read once (non-temporal).
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc_of(const void *base)
-{
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), (short)0, 0x7fffffff, 0x00020000);
-}
-#define DV_NT 2
-
-// ---------------------------------------------------------------------------
-// V cache layout: per (layer, head), 32-slot tiles one after another, each
-// tile dim-major ([hd][32]): entry (dim j, slot s) at element
-// ((s / 32) hd + j) 32 + s % 32 of the head, so one tile of 32 keys is one
-// contiguous hd x 64-byte block and 8 consecutive slots of a dim are 16
-// contiguous bytes (the PV B-operand).
-
-__device__ __forceinline__ size_t v_index(int j, int s, int hd)
-{
-    return ((size_t)(s >> 5) * hd + j) * 32 + (s & 31);
-}
-
-// ---------------------------------------------------------------------------
-// split layout of activations (see dv_internal.h)
-
-// MT = 0 selects the half layout (tokens 0-7 only; lo in columns 8-15).
-__device__ __forceinline__ size_t split_index(int m, int k, int MT)
-{
-    const int s = k >> 5, g = (k >> 3) & 3, j = k & 7, mt = m >> 4, n = m & 15;
-    const size_t blk = MT ? ((size_t)s * MT + mt) * 2 : (size_t)s;
-    return (blk * 64 + g * 16 + n) * 8 + j;  // hi; lo is + split_lo(MT)
-}
-
-__device__ __forceinline__ int split_lo(int MT) { return MT ? 512 : 64; }
-
-// token tiles of a split-layout operand (0: half layout) and the tokens it
-// holds
-__device__ __forceinline__ int split_mt(int Mpad, int half) { return half ? 0 : Mpad >> 4; }
-__device__ __forceinline__ int split_rows(int Mpad, int half) { return half ? 8 : Mpad; }
-
-__device__ __forceinline__ void store_split(uint16_t *xs, int m, int k, int MT, float v)
-{
-    const size_t i = split_index(m, k, MT);
-    const float hi = __uint_as_float(__float_as_uint(v) & 0xffff0000u);
-    xs[i] = (uint16_t)(__float_as_uint(v) >> 16);
-    xs[i + split_lo(MT)] = f2bf(v - hi);
-}
-
-// fp32 -> bf16 hi (truncation) + lo (RNE of the remainder), 8 values
-__device__ __forceinline__ void split_hi_lo(const float4 &a, const float4 &b, bf16x8 &hi, bf16x8 &lo)
-{
-    const float v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const float h = __uint_as_float(__float_as_uint(v[i]) & 0xffff0000u);
-        hi[i] = (__bf16)h;
-        lo[i] = (__bf16)(v[i] - h);
-    }
-}
-
-// four consecutive columns k..k+3 (k % 4 == 0) of one token
-__device__ __forceinline__ void store_split4(uint16_t *xs, int m, int k, int MT, float4 v)
-{
-    const size_t i = split_index(m, k, MT);
-    const float f[4] = {v.x, v.y, v.z, v.w};
-    uint32_t hi[2], lo[2];
-#pragma unroll
-    for (int p = 0; p < 2; ++p) {
-        uint32_t h2 = 0, l2 = 0;
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const float x = f[2 * p + q];
-            const float h = __uint_as_float(__float_as_uint(x) & 0xffff0000u);
-            h2 |= (__float_as_uint(x) >> 16) << (16 * q);
-            l2 |= (uint32_t)f2bf(x - h) << (16 * q);
-        }
-        hi[p] = h2;
-        lo[p] = l2;
-    }
-    *reinterpret_cast<uint2 *>(xs + i) = make_uint2(hi[0], hi[1]);
-    *reinterpret_cast<uint2 *>(xs + i + split_lo(MT)) = make_uint2(lo[0], lo[1]);
-}
 
 // ---------------------------------------------------------------------------
 // Projection rows.  A 32-row tile is two 16-row halves (MFMA blocks) mapped to
@@ -178,21 +70,78 @@ __device__ __forceinline__ RowMap row_map(const GemmArgs &a, int epi, int t)
     return m;
 }
 
-__device__ __forceinline__ float silu(float z) { return z / (1.0f + expf(-z)); }
-
 // ---------------------------------------------------------------------------
 // Projection epilogues.  Y[m * ld + r] (m < Mpad, r < rows) holds the
 // complete sums of one row group's rows for token m.
 
 // 1/rms of each token of the input from the producer's partial sums of
-// squares, in a fixed order: TPT threads per token each sum every TPT-th
-// partial, then a butterfly.  In two parts: rinv_load issues a thread's first
-// NJ partials before the weight stream starts (a wave's loads return in order,
-// so they are back before the first weights and waiting for them empties
-// nothing), rinv_finish consumes them once the first weight steps have been
-// requested.  All threads share the work: with 4 threads per token (20 loads
-// each at d = 5120, branched on) one wave's stream started late and the
-// others waited for it at the end.
+// squares, in a fixed order: thread 4 m + c sums partials c, c + 4, ...
+// (loads issued together), then the four chains are combined by shuffles.
+// Needs 4 Mpad <= blockDim.x; writes rinv[0..Mpad).
+__device__ __forceinline__ void input_rinv(const GemmArgs &a, float *rinv)
+{
+    constexpr int NJ = 32;  // loads in flight per thread
+    const int tid = threadIdx.x, m = tid >> 2, c = tid & 3;
+    float s = 0.f;
+    if (m < a.Mpad) {
+        const float *p = a.ssq_in + (size_t)m * a.n_ssq_in;
+        for (int base = 0; base < a.n_ssq_in; base += 4 * NJ) {
+            float v[NJ];
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+                const int i = base + c + 4 * j;
+                v[j] = i < a.n_ssq_in ? p[i] : 0.f;
+            }
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) s += v[j];
+        }
+    }
+    s += __shfl_xor(s, 1);
+    s += __shfl_xor(s, 2);
+    if (m < a.Mpad && c == 0) rinv[m] = m < a.M ? 1.0f / sqrtf(s / (float)a.dn + a.eps) : 0.f;
+}
+
+// The same 1/rms in two parts, for the projections: rinv_load issues the
+// first NJ partials of each thread before the weight stream starts (loads
+// return in order, so they arrive first and no later wait on them drains the
+// stream); rinv_finish, after the stream, adds the remaining partials in the
+// same order and writes rinv (bit-identical to input_rinv).
+template <int NJ>
+__device__ __forceinline__ void rinv_load(const GemmArgs &a, float (&v)[NJ])
+{
+    const int tid = threadIdx.x, m = tid >> 2, c = tid & 3;
+    const float *p = a.ssq_in + (size_t)m * a.n_ssq_in;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+        const int i = c + 4 * j;
+        v[j] = (m < a.Mpad && i < a.n_ssq_in) ? p[i] : 0.f;
+    }
+}
+
+template <int NJ>
+__device__ __forceinline__ void rinv_finish(const GemmArgs &a, const float (&v)[NJ], float *rinv)
+{
+    const int tid = threadIdx.x, m = tid >> 2, c = tid & 3;
+    float s = 0.f;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) s += v[j];
+    if (m < a.Mpad) {
+        const float *p = a.ssq_in + (size_t)m * a.n_ssq_in;
+        for (int i = c + 4 * NJ; i < a.n_ssq_in; i += 4) s += p[i];
+    }
+    s += __shfl_xor(s, 1);
+    s += __shfl_xor(s, 2);
+    if (m < a.Mpad && c == 0) rinv[m] = m < a.M ? 1.0f / sqrtf(s / (float)a.dn + a.eps) : 0.f;
+}
+
+// The same for the fp32 projections, by all threads: TPT per token each sum
+// every TPT-th partial (fixed order), then a butterfly.  load issues a
+// thread's first NJ partials before the weight stream starts (a wave's loads
+// return in order, so they are back before the first weights and waiting for
+// them empties nothing), finish consumes them once the first weight steps
+// have been requested.  7B, 16 nodes: QKV 48 -> 38 us, gate/up 79 -> 71,
+// lm_head 88 -> 78 against input_rinv with clamped loads; the bf16 and int8
+// kernels gain under 1% and keep the order above.
 template <int NT, int MT> struct Rinv {
     static constexpr int TPT = NT / (MT == 1 ? 16 : (MT == 2 ? 32 : 64));
     static constexpr int NJ = TPT >= 16 ? 8 : (TPT >= 8 ? 12 : 24);
@@ -627,23 +576,13 @@ __global__ __launch_bounds__(16) void k_pack_scales(GemmArgs a, int epi, float *
     dst[gb * 16 + r] = sc[rm.row0[h] + r];
 }
 
-// Four int8 values -> four bf16 (exact: |q| <= 128 needs 8 significant bits),
-// two per dword, low byte first.
-__device__ __forceinline__ uint2 i8x4_to_bf16(uint32_t d)
-{
-    const uint32_t f0 = __float_as_uint((float)(int8_t)(d & 0xff));
-    const uint32_t f1 = __float_as_uint((float)(int8_t)((d >> 8) & 0xff));
-    const uint32_t f2 = __float_as_uint((float)(int8_t)((d >> 16) & 0xff));
-    const uint32_t f3 = __float_as_uint((float)(int8_t)(d >> 24));
-    return make_uint2(__builtin_amdgcn_perm(f1, f0, 0x07060302u), __builtin_amdgcn_perm(f3, f2, 0x07060302u));
-}
-
 template <int MT_, int EPI, typename KV, int NW, int U, int RB, bool Q8 = false>
 __global__ __launch_bounds__(64 * NW) void k_proj(GemmArgs a)
 {
     constexpr bool HALF = MT_ == 0;
     constexpr int MT = HALF ? 1 : MT_;  // token tiles of the MFMA outputs
     constexpr int ROWS = RB * 16, LD = ROWS + 1, NE = RB * MT * 64;
+    static_assert(64 * NW >= 4 * 16 * MT, "input_rinv needs 4 threads per token");
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, tid = threadIdx.x;
     // a step is one k-step of 32 (bf16 weights) or a pair of them (int8);
     // XP activation blocks per step and token tile (PP parts per k-step)
@@ -665,8 +604,14 @@ __global__ __launch_bounds__(64 * NW) void k_proj(GemmArgs a)
     // loads return in order, so they are back before the first weights and no
     // wait for them empties the stream.
     constexpr bool NEED_RINV = EPI != EPI_RESID && EPI != EPI_PLAIN;
-    using RV = Rinv<64 * NW, MT>;
+    constexpr int NJP = MT >= 2 ? 8 : 24;                            // norm partials per thread
     constexpr int SXN = (16 * MT * ROWS + 64 * NW - 1) / (64 * NW);  // RESID: x values per thread
+    // QKV and gate/up compute the input's 1/rms right after requesting their
+    // first weight steps, so every wave waits for those steps before
+    // streaming on; measured faster than preloading the partials (13B: QKV
+    // 28.0 -> 26.9 us, gate/up 44.5 -> 43.6 us), while lm_head is faster
+    // with the preload (51.4 against 53.2 us)
+    constexpr bool RINV_FIRST = EPI == EPI_QKV || EPI == EPI_SWIGLU;
     static_assert(ROWS <= 64 * NW, "one gain per thread");
 
     for (int unit = blockIdx.x; unit < a.n_units; unit += gridDim.x) {
@@ -689,7 +634,8 @@ __global__ __launch_bounds__(64 * NW) void k_proj(GemmArgs a)
             for (int mt = 0; mt < MT; ++mt) acc[b][mt] = (f32x4){0.f, 0.f, 0.f, 0.f};
         f32x4 rs[Q8 ? RB : 1];  // int8: this lane's four row scales per block
         float sx[EPI == EPI_RESID ? SXN : 1], sgain = 0.f;
-        float sv[RV::NJ];
+        float sv[NEED_RINV ? NJP : 1];
+        const bool load_rinv = NEED_RINV && !have_rinv;
         if constexpr (EPI == EPI_RESID) {
 #pragma unroll
             for (int c = 0; c < SXN; ++c) {
@@ -698,8 +644,8 @@ __global__ __launch_bounds__(64 * NW) void k_proj(GemmArgs a)
             }
             if (tid < ROWS) sgain = Elem<uint16_t>::load(reinterpret_cast<const uint16_t *>(a.gain), g * ROWS + tid);
         }
-        if constexpr (NEED_RINV) {
-            if (!have_rinv) RV::load(a, sv);
+        if constexpr (NEED_RINV && !RINV_FIRST) {
+            if (load_rinv) rinv_load<NJP>(a, sv);
         }
         if (n > 0) {
             u32x4 wb[U][RB], xb[U][MT][XP];
@@ -744,11 +690,12 @@ __global__ __launch_bounds__(64 * NW) void k_proj(GemmArgs a)
                 for (int b = 0; b < RB; ++b)
                     rs[b] = *reinterpret_cast<const f32x4 *>(a.scale + (g * RB + b) * 16 + 4 * (lane >> 4));
             }
-            __builtin_amdgcn_sched_barrier(0);
-            if constexpr (NEED_RINV) {
+            if constexpr (RINV_FIRST) {
                 // the first unit's weight steps are in flight
-                if (!have_rinv) RV::finish(a, sv, rinv);
-                have_rinv = true;
+                if (!have_rinv) {
+                    input_rinv(a, rinv);
+                    have_rinv = true;
+                }
             }
             int i = 0;
             for (; i + U < n; i += U) {
@@ -782,9 +729,17 @@ __global__ __launch_bounds__(64 * NW) void k_proj(GemmArgs a)
             }
             if (tid < ROWS) stage_s[tid] = sgain;
         }
-        if constexpr (NEED_RINV) {
-            if (!have_rinv) RV::finish(a, sv, rinv);  // no k-step of the unit for this wave
-            have_rinv = true;
+        if constexpr (NEED_RINV && !RINV_FIRST) {
+            if (load_rinv) {
+                rinv_finish<NJP>(a, sv, rinv);
+                have_rinv = true;
+            }
+        }
+        if constexpr (RINV_FIRST) {
+            if (!have_rinv) {  // a unit without k-steps for this workgroup's waves
+                input_rinv(a, rinv);
+                have_rinv = true;
+            }
         }
 
         // wave partials -> unit sums (fixed wave order)
@@ -1215,7 +1170,7 @@ __global__ __launch_bounds__(DV_NORM_THREADS) void k_embed_norm(NormArgs a)
 // leaves room for 8 waves when a split has at most one tile per wave.
 // QT query tiles of 16 are held at once (M <= 16 QT): every loaded key tile
 // serves all of them, each with its own running max, sum and output.
-template <int HD, int NW, bool DB, int QT, typename KV = uint16_t>
+template <int HD, int NW, bool DB, int QT, typename KV>
 __global__ __launch_bounds__(64 * NW) void k_attn_mfma(AttnArgs a)
 {
     constexpr bool F32 = sizeof(KV) == 4;
@@ -1886,476 +1841,7 @@ __global__ __launch_bounds__(SAMPLE_THREADS) void k_accept_sampled(SampleArgs a)
     }
 }
 
-// ---------------------------------------------------------------------------
-// Large-M prefill: a prompt chunk of M tokens (padded to Mp, a multiple of
-// 128) in one causal pass.  The projections are a dense contraction here, so
-// they run on an MFMA GEMM over the packed weights of the verify path (block
-// (k-step s, 16-row block gb) at (s NB + gb) 512) and split-layout
-// activations of the whole chunk (MT = Mp / 16 token tiles), with the verify
-// path's epilogues fused: rotary + K/V write, SwiGLU, residual + the next
-// norm's input.  Every norm's 1/rms, a per-token scalar, is applied by its
-// consumer's epilogue from sums of squares over 64-row slices (Mp x d / 64
-// partials), so no fp32 GEMM output goes through HBM.
-
-constexpr int PF_THREADS = 256;
-
-// Embedding rows of the chunk: x = E[token], the first norm's numerator
-// x * gain in split layout and the sums of squares of 64-column slices;
-// tokens >= M get zeros.  One workgroup per token, 4 columns per thread.
-__global__ __launch_bounds__(PF_THREADS) void k_pf_embed(const int32_t *tokens, const uint16_t *embed, int M, int d,
-                                                         int MT, const uint16_t *gain, float *x, uint16_t *us,
-                                                         float *ssq)
-{
-    const int m = blockIdx.x, nsq = d / 64;
-    for (int k = 4 * threadIdx.x; k < d; k += 4 * PF_THREADS) {
-        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (m < M) {
-            const uint2 e = *reinterpret_cast<const uint2 *>(embed + (size_t)tokens[m] * d + k);
-            v = make_float4(__uint_as_float(e.x << 16), __uint_as_float(e.x & 0xffff0000u), __uint_as_float(e.y << 16),
-                            __uint_as_float(e.y & 0xffff0000u));
-        }
-        *reinterpret_cast<float4 *>(x + (size_t)m * d + k) = v;
-        store_split4(us, m, k, MT,
-                     make_float4(v.x * bf2f(gain[k]), v.y * bf2f(gain[k + 1]), v.z * bf2f(gain[k + 2]),
-                                 v.w * bf2f(gain[k + 3])));
-        // 16 neighbouring threads hold one 64-column slice
-        float ss = fmaf(v.x, v.x, fmaf(v.y, v.y, fmaf(v.z, v.z, v.w * v.w)));
-        ss += __shfl_xor(ss, 1);
-        ss += __shfl_xor(ss, 2);
-        ss += __shfl_xor(ss, 4);
-        ss += __shfl_xor(ss, 8);
-        if ((threadIdx.x & 15) == 0) ssq[(size_t)m * nsq + k / 64] = ss;
-    }
-}
-
-// The prefill GEMM.  Workgroup = NWR x NWT waves over 64 NWR rows (4 blocks
-// per wave) x 16 TT NWT tokens (TT token tiles per wave).  Per k-step each
-// wave loads its 4 weight blocks into registers, the workgroup stages the
-// activation slab of its token tiles (hi + lo) in LDS, and each wave runs
-// 8 TT MFMAs (16x16x32 bf16, hi and lo into the same accumulator).  A
-// wave's loads return in order, so weights and activations share one lead
-// of LEAD k-steps (activations first in each step's loads).  With BPRE the
-// slab is stashed two k-steps ahead into three LDS buffers and each wave
-// reads its B operands one k-step ahead into registers; without it the slab
-// is stashed one k-step ahead into two buffers and read just before use.
-template <int EPI, int NWR, int NWT, int TT, int LEAD, bool BPRE>
-__global__ __launch_bounds__(64 * NWR * NWT) void k_pf_gemm(PfArgs a)
-{
-    constexpr int NW = NWR * NWT, NT = 64 * NW, BW = 4, XT = NWT * TT, NBUF = BPRE ? 3 : 2;
-    // the activation slab of a k-step: XE u32x4 (hi + lo of XT token
-    // tiles), XL of them staged per thread (whole waves idle past XE)
-    constexpr int XE = XT * 2 * 64, XL = (XE + NT - 1) / NT;
-    static_assert(LEAD >= (BPRE ? 3 : 2), "the stash needs its loads a k-step earlier");
-    // k-steps per unrolled round: register slots (st % LEAD) and B register
-    // sets (st % 2) are compile-time in it
-    constexpr int UR = (BPRE && LEAD % 2) ? 2 * LEAD : LEAD;
-    __shared__ u32x4 xsm[NBUF][XT * 2 * 64];
-    __shared__ float rinv_s[16 * XT];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, tid = threadIdx.x;
-    const int wr = wave % NWR, wt = wave / NWR;
-    // 1-D grid, XCD-aware: workgroups are dispatched to the 8 XCDs round
-    // robin (workgroup b to XCD b % 8, 32 CUs each), so XCD x takes tiles
-    // [x per, (x + 1) per) of the row-tile-major order: every XCD gets the
-    // same count, and the token groups of a row tile share one XCD's L2 for
-    // the row tile's weights (at most two XCDs at a chunk boundary).  Token
-    // groups of XT tiles; the last one may be short (its missing tiles
-    // re-read the last token tile and are never stored).
-    const int n_tt = (a.MT + XT - 1) / XT, n_rt = (a.NB + NWR * BW - 1) / (NWR * BW);
-    const int n_tiles = n_rt * n_tt, per = (n_tiles + 7) / 8;
-    const int L = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
-    if (L >= n_tiles) return;  // padding of the grid to 8 x per
-    const int rtile = L / n_tt;
-    const int tt0 = (L - rtile * n_tt) * XT;                 // first token tile of the workgroup
-    const int gb0 = (rtile * NWR + wr) * BW;                 // first block of this wave
-    const int S = a.K / 32;
-    if (EPI != EPI_RESID) {
-        for (int m = tid; m < 16 * min(XT, a.MT - tt0); m += NT) {
-            const float *p = a.ssq_in + (size_t)(tt0 * 16 + m) * a.nsq_in;
-            float sum = 0.f;
-            for (int c = 0; c < a.nsq_in; ++c) sum += p[c];
-            rinv_s[m] = 1.0f / sqrtf(sum / (float)a.d + a.eps);
-        }
-    }
-    // buffer loads: the per-lane byte offsets stay fixed, a scalar offset moves
-    // by one k-step (so no address register is rewritten while a load into a
-    // neighbouring register is in flight); blocks past NB re-read the last
-    // block (their sums are dropped)
-    const __amdgpu_buffer_rsrc_t rw = rsrc_of(a.packed), rx = rsrc_of(a.xs);
-    uint32_t wofs[BW], xofs[XL];
-#pragma unroll
-    for (int b = 0; b < BW; ++b) wofs[b] = (uint32_t)(min(gb0 + b, a.NB - 1) * 1024 + lane * 16);
-#pragma unroll
-    for (int i = 0; i < XL; ++i) {
-        const int e = min(tid + NT * i, XE - 1), tile = min(tt0 + e / 128, a.MT - 1);
-        xofs[i] = (uint32_t)((tile * 128 + e % 128) * 16);
-    }
-    const uint32_t wstep = (uint32_t)a.NB * 1024u, xstep = (uint32_t)a.MT * 2048u;
-    u32x4 wb[LEAD][BW], stg[LEAD][XL];
-    auto fetch = [&](int j, int st) {
-#pragma unroll
-        for (int i = 0; i < XL; ++i)
-            stg[j][i] = __builtin_amdgcn_raw_buffer_load_b128(rx, xofs[i], (uint32_t)st * xstep, 0);
-#pragma unroll
-        for (int b = 0; b < BW; ++b)
-            wb[j][b] = __builtin_amdgcn_raw_buffer_load_b128(rw, wofs[b], (uint32_t)st * wstep, DV_NT);
-    };
-    auto stash = [&](int j, int buf) {
-#pragma unroll
-        for (int i = 0; i < XL; ++i)
-            if (XE % NT == 0 || tid + NT * i < XE) xsm[buf][tid + NT * i] = stg[j][i];
-    };
-    f32x4 acc[BW][TT];
-#pragma unroll
-    for (int b = 0; b < BW; ++b)
-#pragma unroll
-        for (int t = 0; t < TT; ++t) acc[b][t] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    auto mma = [&](int j, int t, const u32x4 &hv, const u32x4 &lv) {
-        const bf16x8 hi = __builtin_bit_cast(bf16x8, hv), lo = __builtin_bit_cast(bf16x8, lv);
-#pragma unroll
-        for (int b = 0; b < BW; ++b) {
-            const bf16x8 w = __builtin_bit_cast(bf16x8, wb[j][b]);
-            acc[b][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, hi, acc[b][t], 0, 0, 0);
-            acc[b][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, lo, acc[b][t], 0, 0, 0);
-        }
-    };
-    auto xat = [&](int buf, int t, int q) -> u32x4 { return xsm[buf][((wt * TT + t) * 2 + q) * 64 + lane]; };
-    // Loads and stashes are issued unconditionally (k-steps past the end
-    // re-read the last one and are never used), so the number of loads in
-    // flight behind each one is the same on every path and every wait is the
-    // one the pipeline needs.  K-step st: weights in register slot st % LEAD.
-#pragma unroll
-    for (int j = 0; j < LEAD; ++j) fetch(j, min(j, S - 1));
-    if constexpr (BPRE) {
-        // activations in LDS buffer st % 3, stashed two k-steps ahead; B
-        // operands in register set st % 2, read one k-step ahead.  The
-        // barrier after step st makes step st + 2's stash visible, and every
-        // read of buffer (st + 3) % 3 (step st's operands, read in step
-        // st - 1) is done before step st + 1 overwrites it.
-        u32x4 xb[2][TT][2];
-        auto bread = [&](int r, int buf) {
-#pragma unroll
-            for (int t = 0; t < TT; ++t)
-#pragma unroll
-                for (int q = 0; q < 2; ++q) xb[r][t][q] = xat(buf, t, q);
-        };
-        stash(0, 0);
-        stash(1, 1);
-        __syncthreads();
-        bread(0, 0);
-        for (int s0 = 0; s0 < S; s0 += UR) {
-#pragma unroll
-            for (int u = 0; u < UR; ++u) {
-                const int st = s0 + u, j = u % LEAD;
-                if (st < S) {
-#pragma unroll
-                    for (int t = 0; t < TT; ++t) mma(j, t, xb[u & 1][t][0], xb[u & 1][t][1]);
-                }
-                bread((u + 1) & 1, (st + 1) % 3);
-                stash((u + 2) % LEAD, (st + 2) % 3);
-                fetch(j, min(st + LEAD, S - 1));
-                __syncthreads();
-            }
-        }
-    } else {
-        // activations in LDS buffer st % 2, stashed one k-step ahead; the
-        // barrier after step st makes step st + 1's stash visible, and every
-        // read of buffer st % 2 is done before step st + 1 overwrites it
-        stash(0, 0);
-        __syncthreads();
-        for (int s0 = 0; s0 < S; s0 += UR) {
-#pragma unroll
-            for (int u = 0; u < UR; ++u) {
-                const int st = s0 + u, j = u % LEAD;
-                if (st < S) {
-#pragma unroll
-                    for (int t = 0; t < TT; ++t) mma(j, t, xat(st & 1, t, 0), xat(st & 1, t, 1));
-                }
-                stash((u + 1) % LEAD, (st + 1) & 1);
-                fetch(j, min(st + LEAD, S - 1));
-                __syncthreads();
-            }
-        }
-    }
-
-    // ---- epilogues: lane l holds rows 4 (l / 16) + jj of block gb0 + b for
-    // token (tt0 + wt TT + t) 16 + l % 16
-    const int n16 = lane & 15, r4 = 4 * (lane >> 4);
-    if (EPI == EPI_QKV) {
-        const int per_seg = a.d / DV_GEMM_TILE, per_head = a.hd / DV_GEMM_TILE, half = a.hd / 2;
-#pragma unroll
-        for (int p = 0; p < BW / 2; ++p) {
-            const int gb = gb0 + 2 * p;
-            if (gb >= a.NB) break;
-            const int tile = gb >> 1, seg = tile / per_seg, tt = tile - seg * per_seg;
-            const int h = tt / per_head, j0 = (tt - h * per_head) * 16 + r4;
-#pragma unroll
-            for (int t = 0; t < TT; ++t) {
-                const int ml = (wt * TT + t) * 16 + n16, m = tt0 * 16 + ml;
-                if (m >= a.M) continue;
-                const float ri = rinv_s[ml];
-                float y1[4], y2[4];
-#pragma unroll
-                for (int jj = 0; jj < 4; ++jj) {
-                    y1[jj] = acc[2 * p][t][jj] * ri;
-                    y2[jj] = acc[2 * p + 1][t][jj] * ri;
-                }
-                const int pos = a.P0 + m;
-                if (seg < 2) {
-#pragma unroll
-                    for (int jj = 0; jj < 4; ++jj) {
-                        const float c = a.rope_cos[(size_t)pos * half + j0 + jj];
-                        const float sn = a.rope_sin[(size_t)pos * half + j0 + jj];
-                        const float o1 = y1[jj] * c - y2[jj] * sn, o2 = y2[jj] * c + y1[jj] * sn;
-                        y1[jj] = o1;
-                        y2[jj] = o2;
-                    }
-                }
-                if (seg == 0) {
-                    float *qr = a.q + (size_t)m * a.d + h * a.hd + j0;
-                    *reinterpret_cast<float4 *>(qr) = make_float4(y1[0], y1[1], y1[2], y1[3]);
-                    *reinterpret_cast<float4 *>(qr + half) = make_float4(y2[0], y2[1], y2[2], y2[3]);
-                } else if (seg == 1) {  // K: [H][cap][hd]
-                    uint16_t *kr = reinterpret_cast<uint16_t *>(a.kc) + ((size_t)h * a.cap + pos) * a.hd + j0;
-                    *reinterpret_cast<uint2 *>(kr) = make_uint2(f2bf(y1[0]) | (uint32_t)f2bf(y1[1]) << 16,
-                                                                f2bf(y1[2]) | (uint32_t)f2bf(y1[3]) << 16);
-                    *reinterpret_cast<uint2 *>(kr + half) = make_uint2(f2bf(y2[0]) | (uint32_t)f2bf(y2[1]) << 16,
-                                                                       f2bf(y2[2]) | (uint32_t)f2bf(y2[3]) << 16);
-                } else {                // V: [H][cap/32][hd][32]
-                    uint16_t *vh = reinterpret_cast<uint16_t *>(a.vc) + (size_t)h * a.hd * a.cap;
-#pragma unroll
-                    for (int jj = 0; jj < 4; ++jj) {
-                        vh[v_index(j0 + jj, pos, a.hd)] = f2bf(y1[jj]);
-                        vh[v_index(j0 + jj + half, pos, a.hd)] = f2bf(y2[jj]);
-                    }
-                }
-            }
-        }
-    } else if (EPI == EPI_SWIGLU) {
-        // gate block 2p and up block 2p + 1 hold h columns 16 (gb / 2) + ...
-#pragma unroll
-        for (int p = 0; p < BW / 2; ++p) {
-            const int gb = gb0 + 2 * p;
-            if (gb >= a.NB) break;
-            const int f0 = 16 * (gb >> 1) + r4;
-#pragma unroll
-            for (int t = 0; t < TT; ++t) {
-                if (tt0 + wt * TT + t >= a.MT) break;  // a short last token group
-                const int ml = (wt * TT + t) * 16 + n16, m = tt0 * 16 + ml;
-                float hv[4] = {0.f, 0.f, 0.f, 0.f};
-                if (m < a.M) {
-                    const float ri = rinv_s[ml];
-#pragma unroll
-                    for (int jj = 0; jj < 4; ++jj) hv[jj] = silu(acc[2 * p][t][jj] * ri) * (acc[2 * p + 1][t][jj] * ri);
-                }
-                store_split4(a.hs, m, f0, a.MT, make_float4(hv[0], hv[1], hv[2], hv[3]));
-            }
-        }
-    } else {  // EPI_RESID
-        if (gb0 < a.NB) {
-            const int nsq = a.d / 64;
-#pragma unroll
-            for (int t = 0; t < TT; ++t) {
-                if (tt0 + wt * TT + t >= a.MT) break;  // a short last token group (wave-uniform)
-                const int ml = (wt * TT + t) * 16 + n16, m = tt0 * 16 + ml;
-                float ss = 0.f;
-#pragma unroll
-                for (int b = 0; b < BW; ++b) {
-                    const int r = 16 * (gb0 + b) + r4;
-                    float4 xv = make_float4(0.f, 0.f, 0.f, 0.f);
-                    if (m < a.M) {
-                        float *xp = a.x + (size_t)m * a.d + r;
-                        xv = *reinterpret_cast<const float4 *>(xp);
-                        xv.x += acc[b][t][0];
-                        xv.y += acc[b][t][1];
-                        xv.z += acc[b][t][2];
-                        xv.w += acc[b][t][3];
-                        *reinterpret_cast<float4 *>(xp) = xv;
-                    }
-                    ss = fmaf(xv.x, xv.x, fmaf(xv.y, xv.y, fmaf(xv.z, xv.z, fmaf(xv.w, xv.w, ss))));
-                    store_split4(a.us, m, r, a.MT,
-                                 make_float4(xv.x * bf2f(a.gain[r]), xv.y * bf2f(a.gain[r + 1]),
-                                             xv.z * bf2f(a.gain[r + 2]), xv.w * bf2f(a.gain[r + 3])));
-                }
-                ss += __shfl_xor(ss, 16);
-                ss += __shfl_xor(ss, 32);
-                if (lane < 16) a.ssq_out[(size_t)m * nsq + gb0 / 4] = ss;
-            }
-        }
-    }
-}
-
-// Causal attention of the chunk's queries (positions P0 + i) over cache slots
-// [0, P0 + i].  Workgroup = 64 queries of one head, each wave 16 of them; the
-// workgroup stages every 32-key tile up to its last query in LDS once (K rows
-// and the tile's V block, rows padded against bank conflicts; the next tile's
-// global loads are in flight while the current one is used), and each wave
-// uses the tiles up to its own last query.  The scores and the running
-// softmax follow the tree-attention kernel (MFMA with q split in hi + lo,
-// exp2 in log2 units); the output goes to the O projection's operand (split
-// layout of MT token tiles).  Grid (heads, query blocks) with the last query
-// block first: workgroups are dispatched in order, so the longest ones (the
-// most keys) start first and the short ones fill in behind them.
-template <int HD>
-__global__ __launch_bounds__(256) void k_attn_causal(const float *q, const uint16_t *kc_l, const uint16_t *vc_l,
-                                                     int M, int P0, int H, int cap, int MT, uint16_t *out)
-{
-    constexpr int NC = HD / 32, ND = HD / 16;
-    constexpr int KROW = HD * 2 + 16;          // bytes per staged key row (padded)
-    constexpr int VROW = 80;                   // bytes per staged dim row of 32 values (padded)
-    constexpr int KBYTES = 32 * KROW, VBYTES = HD * VROW;
-    constexpr int KCH = 32 * HD / 8, VCH = HD * 4;  // 16-byte chunks of a tile's K and V
-    constexpr int CPT = (KCH + VCH + 255) / 256;     // chunks per thread
-    __shared__ __align__(16) unsigned char smem[2][KBYTES + VBYTES];
-    const int h = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int n = lane & 15, g = lane >> 4;
-    const int q0 = (gridDim.y - 1 - blockIdx.y) * 64;
-    const int qb = q0 + wave * 16;               // first query of this wave
-    const int D = H * HD;
-    const int kend_wg = P0 + min(q0 + 64, M);    // keys the workgroup may see
-    const int ntile = (kend_wg + 31) / 32;
-    const bool active = qb < M;
-    const int kend = P0 + min(qb + 16, M);       // keys this wave may see
-    const int wtiles = active ? (kend + 31) / 32 : 0;
-    const float scale2 = 1.4426950408889634f / sqrtf((float)HD);
-    const uint16_t *kc = kc_l + (size_t)h * cap * HD;
-    const uint16_t *vc = vc_l + (size_t)h * HD * cap;
-    const int qi = min(qb + n, M - 1);          // this lane's query (B operand column)
-    const int lim = P0 + qb + n;                // last key it sees
-
-    bf16x8 qh[NC], ql[NC];
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-        const float *qp = q + (size_t)qi * D + h * HD + 32 * c + 8 * g;
-        split_hi_lo(*reinterpret_cast<const float4 *>(qp), *reinterpret_cast<const float4 *>(qp + 4), qh[c], ql[c]);
-    }
-    // global -> registers -> LDS staging of tile t: chunk e < KCH is 16 bytes
-    // of key row e / (HD / 8) (rows past the workgroup's last key repeat it),
-    // the rest 16 bytes of the tile's V block (dim row, 8 slots)
-    u32x4 stg[CPT];
-    auto fetch = [&](int t) {
-        const int k0 = 32 * t;
-#pragma unroll
-        for (int i = 0; i < CPT; ++i) {
-            const int e = tid + 256 * i;
-            if (e < KCH) {
-                const int r = e / (HD / 8), c8 = e % (HD / 8);
-                const int key = min(k0 + r, kend_wg - 1);
-                stg[i] = *reinterpret_cast<const u32x4 *>(kc + (size_t)key * HD + 8 * c8);
-            } else if (e < KCH + VCH) {
-                const int ev = e - KCH;
-                stg[i] = *reinterpret_cast<const u32x4 *>(vc + (size_t)(k0 >> 5) * HD * 32 + 8 * ev);
-            }
-        }
-    };
-    auto stash = [&](int buf) {
-#pragma unroll
-        for (int i = 0; i < CPT; ++i) {
-            const int e = tid + 256 * i;
-            if (e < KCH) {
-                const int r = e / (HD / 8), c8 = e % (HD / 8);
-                *reinterpret_cast<u32x4 *>(&smem[buf][r * KROW + 16 * c8]) = stg[i];
-            } else if (e < KCH + VCH) {
-                const int ev = e - KCH, dr = ev >> 2, c8 = ev & 3;
-                *reinterpret_cast<u32x4 *>(&smem[buf][KBYTES + dr * VROW + 16 * c8]) = stg[i];
-            }
-        }
-    };
-
-    float m_run = -INFINITY, l_run = 0.f;
-    f32x4 o[ND];
-#pragma unroll
-    for (int dt = 0; dt < ND; ++dt) o[dt] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    auto process = [&](int t, int buf) {
-        const int k0 = 32 * t;
-        const unsigned char *ks = smem[buf], *vs = smem[buf] + KBYTES;
-        const int ra = 8 * (n >> 2) + (n & 3), rb = ra + 4;
-        f32x4 sa = (f32x4){0.f, 0.f, 0.f, 0.f}, sb = sa;
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            const bf16x8 ka8 = *reinterpret_cast<const bf16x8 *>(ks + ra * KROW + 64 * c + 16 * g);
-            const bf16x8 kb8 = *reinterpret_cast<const bf16x8 *>(ks + rb * KROW + 64 * c + 16 * g);
-            sa = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka8, qh[c], sa, 0, 0, 0);
-            sb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kb8, qh[c], sb, 0, 0, 0);
-            sa = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka8, ql[c], sa, 0, 0, 0);
-            sb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kb8, ql[c], sb, 0, 0, 0);
-        }
-        // scores of query (lane n) for keys k0 + 8g + i
-        float sv[8], mt = -INFINITY;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int key = k0 + 8 * g + i;
-            const float sc = (i < 4 ? sa[i] : sb[i - 4]) * scale2;
-            sv[i] = key <= lim ? sc : -INFINITY;
-            mt = fmaxf(mt, sv[i]);
-        }
-        mt = fmaxf(mt, __shfl_xor(mt, 16));
-        mt = fmaxf(mt, __shfl_xor(mt, 32));
-        const float mnew = fmaxf(m_run, mt);
-        const float alpha = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - mnew);
-        float ps = 0.f, pv[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            pv[i] = sv[i] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(sv[i] - mnew);
-            ps += pv[i];
-        }
-        ps += __shfl_xor(ps, 16);
-        ps += __shfl_xor(ps, 32);
-        l_run = l_run * alpha + ps;
-        m_run = mnew;
-        float al[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) al[j] = __shfl(alpha, 4 * g + j);
-        u32x4 vt[ND];
-#pragma unroll
-        for (int dt = 0; dt < ND; ++dt)
-            vt[dt] = *reinterpret_cast<const u32x4 *>(vs + (dt * 16 + n) * VROW + 16 * g);
-        if (k0 + 32 > kend) {
-            // slots past the wave's last key hold nothing of this chunk yet
-#pragma unroll
-            for (int dt = 0; dt < ND; ++dt)
-#pragma unroll
-                for (int w = 0; w < 4; ++w) {
-                    const int key = k0 + 8 * g + 2 * w;
-                    uint32_t x = vt[dt][w];
-                    if (key >= kend) x &= 0xffff0000u;
-                    if (key + 1 >= kend) x &= 0x0000ffffu;
-                    vt[dt][w] = x;
-                }
-        }
-        bf16x8 ph, pl;
-        split_hi_lo(make_float4(pv[0], pv[1], pv[2], pv[3]), make_float4(pv[4], pv[5], pv[6], pv[7]), ph, pl);
-#pragma unroll
-        for (int dt = 0; dt < ND; ++dt) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) o[dt][j] *= al[j];
-            const bf16x8 v8 = __builtin_bit_cast(bf16x8, vt[dt]);
-            o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ph, v8, o[dt], 0, 0, 0);
-            o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pl, v8, o[dt], 0, 0, 0);
-        }
-    };
-    fetch(0);
-    stash(0);
-    __syncthreads();
-    for (int t = 0; t < ntile; ++t) {
-        const int buf = t & 1;
-        if (t + 1 < ntile) fetch(t + 1);  // in flight while tile t is used
-        if (t < wtiles) process(t, buf);
-        if (t + 1 < ntile) stash(buf ^ 1);
-        __syncthreads();
-    }
-    if (!active) return;
-    // rows of o are queries qb + 4g + j; their sums l sit in lanes 4g + j
-    float lr[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) lr[j] = __shfl(l_run, 4 * g + j);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int i = qb + 4 * g + j;
-        if (i >= M) continue;
-#pragma unroll
-        for (int dt = 0; dt < ND; ++dt) store_split(out, i, h * HD + dt * 16 + n, MT, o[dt][j] / lr[j]);
-    }
-}
+constexpr int ROW_THREADS = 256;
 
 // ---------------------------------------------------------------------------
 // Draft side.  Dynamic Gated Fusion around three weight-streaming
@@ -2366,11 +1852,11 @@ __global__ __launch_bounds__(256) void k_attn_causal(const float *q, const uint1
 // DGF operands in split layout (the projection kernel's B operand), one
 // workgroup per token row m < Mpad: feature rows and the token embeddings
 // (bf16, so exact: lo = 0); rows n..Mpad are zero.
-__global__ __launch_bounds__(PF_THREADS) void k_dgf_in(const float *feat, const uint16_t *embed, DgfTokens t, int n,
+__global__ __launch_bounds__(ROW_THREADS) void k_dgf_in(const float *feat, const uint16_t *embed, DgfTokens t, int n,
                                                        int d, int MT, uint16_t *xf, uint16_t *xe)
 {
     const int m = blockIdx.x;
-    for (int k = 4 * threadIdx.x; k < d; k += 4 * PF_THREADS) {
+    for (int k = 4 * threadIdx.x; k < d; k += 4 * ROW_THREADS) {
         float4 f = make_float4(0.f, 0.f, 0.f, 0.f), e = f;
         if (m < n) {
             f = *reinterpret_cast<const float4 *>(feat + (size_t)m * d + k);
@@ -2383,11 +1869,11 @@ __global__ __launch_bounds__(PF_THREADS) void k_dgf_in(const float *feat, const 
 }
 
 // gate input [h1 || h2] (K = 2 d) in split layout
-__global__ __launch_bounds__(PF_THREADS) void k_dgf_gate_in(const float *h1, const float *h2, int n, int d, int MT,
+__global__ __launch_bounds__(ROW_THREADS) void k_dgf_gate_in(const float *h1, const float *h2, int n, int d, int MT,
                                                             uint16_t *xg)
 {
     const int m = blockIdx.x;
-    for (int k = 4 * threadIdx.x; k < d; k += 4 * PF_THREADS) {
+    for (int k = 4 * threadIdx.x; k < d; k += 4 * ROW_THREADS) {
         float4 a = make_float4(0.f, 0.f, 0.f, 0.f), b = a;
         if (m < n) {
             a = *reinterpret_cast<const float4 *>(h1 + (size_t)m * d + k);
@@ -2399,11 +1885,11 @@ __global__ __launch_bounds__(PF_THREADS) void k_dgf_gate_in(const float *h1, con
 }
 
 // x0 = g h1 + (1 - g) h2, g = sigmoid(z)
-__global__ __launch_bounds__(PF_THREADS) void k_dgf_mix(const float *z, const float *h1, const float *h2, int d,
+__global__ __launch_bounds__(ROW_THREADS) void k_dgf_mix(const float *z, const float *h1, const float *h2, int d,
                                                         float *x0)
 {
     const int i = blockIdx.x;
-    for (int k = threadIdx.x; k < d; k += PF_THREADS) {
+    for (int k = threadIdx.x; k < d; k += ROW_THREADS) {
         const size_t o = (size_t)i * d + k;
         const float g = 1.f / (1.f + expf(-z[o]));
         x0[o] = g * h1[o] + (1.f - g) * h2[o];
@@ -2411,11 +1897,11 @@ __global__ __launch_bounds__(PF_THREADS) void k_dgf_mix(const float *z, const fl
 }
 
 // Row gather: dst[r] = src[idx[r]] (feature rows of d floats).
-__global__ __launch_bounds__(PF_THREADS) void k_gather_rows(const float *src, RowIndex ix, int d, float *dst)
+__global__ __launch_bounds__(ROW_THREADS) void k_gather_rows(const float *src, RowIndex ix, int d, float *dst)
 {
     const int r = blockIdx.x;
     const float *sp = src + (size_t)ix.idx[r] * d;
-    for (int k = 4 * threadIdx.x; k < d; k += 4 * PF_THREADS)
+    for (int k = 4 * threadIdx.x; k < d; k += 4 * ROW_THREADS)
         *reinterpret_cast<float4 *>(dst + (size_t)r * d + k) = *reinterpret_cast<const float4 *>(sp + k);
 }
 
@@ -2776,61 +2262,11 @@ hipError_t launch_kv_commit(const CommitArgs &a, int kv_bf16, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_pf_embed(const int32_t *tokens, const void *embed, int M, int Mp, int d, const void *gain, float *x,
-                           uint16_t *us, float *ssq, hipStream_t s)
-{
-    if (d % 64 || Mp % 16 || M < 1 || M > Mp) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_pf_embed, dim3(Mp), dim3(PF_THREADS), 0, s, tokens, static_cast<const uint16_t *>(embed), M, d,
-                       Mp / 16, static_cast<const uint16_t *>(gain), x, us, ssq);
-    return hipGetLastError();
-}
-
-#ifndef PF_CFG_MAIN
-#define PF_CFG_MAIN 8, 1, 8, 4, false
-#endif
-#ifndef PF_CFG_RESID
-#define PF_CFG_RESID 8, 1, 3, 4, true
-#endif
-
-template <int EPI, int NWR, int NWT, int TT, int LEAD, bool BPRE>
-static hipError_t pf_launch(const PfArgs &a, hipStream_t s)
-{
-    constexpr int ROWS = 64 * NWR, XT = NWT * TT;
-    // 1-D grid: 8 chunks of ceil(tiles / 8) (token groups x row tiles)
-    const int n_rt = (a.NB * 16 + ROWS - 1) / ROWS, n_tiles = (a.MT + XT - 1) / XT * n_rt;
-    const dim3 grid(8 * ((n_tiles + 7) / 8));
-    hipLaunchKernelGGL((k_pf_gemm<EPI, NWR, NWT, TT, LEAD, BPRE>), grid, dim3(64 * NWR * NWT), 0, s, a);
-    return hipGetLastError();
-}
-
-hipError_t launch_pf_gemm(const PfArgs &a, int epi, hipStream_t s)
-{
-    if (a.K % 32 || a.NB < 1 || a.MT % 8 || a.d % 64 || a.M < 1 || a.M > 16 * a.MT) return hipErrorInvalidValue;
-    if (epi == EPI_RESID) return pf_launch<EPI_RESID, PF_CFG_RESID>(a, s);
-    if (epi == EPI_QKV) {
-        if (a.hd != 64 && a.hd != 128) return hipErrorInvalidValue;
-        return pf_launch<EPI_QKV, PF_CFG_MAIN>(a, s);
-    }
-    if (epi == EPI_SWIGLU) return pf_launch<EPI_SWIGLU, PF_CFG_MAIN>(a, s);
-    return hipErrorInvalidValue;
-}
-
-hipError_t launch_attn_causal(const float *q, const void *kc, const void *vc, int M, int P0, int H, int hd, int cap,
-                              int MT, uint16_t *out, hipStream_t s)
-{
-    const dim3 grid(H, (M + 63) / 64);
-    const uint16_t *k16 = static_cast<const uint16_t *>(kc), *v16 = static_cast<const uint16_t *>(vc);
-    if (hd == 128) hipLaunchKernelGGL(k_attn_causal<128>, grid, dim3(256), 0, s, q, k16, v16, M, P0, H, cap, MT, out);
-    else if (hd == 64) hipLaunchKernelGGL(k_attn_causal<64>, grid, dim3(256), 0, s, q, k16, v16, M, P0, H, cap, MT, out);
-    else return hipErrorInvalidValue;
-    return hipGetLastError();
-}
-
 hipError_t launch_dgf_in(const float *feat, const void *embed, const DgfTokens &t, int n, int Mpad, int d,
                          uint16_t *xf, uint16_t *xe, hipStream_t s)
 {
     if (n < 1 || n > Mpad || Mpad > DV_TREE_MAX || Mpad % 16 || d % 32) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_dgf_in, dim3(Mpad), dim3(PF_THREADS), 0, s, feat, static_cast<const uint16_t *>(embed), t, n, d,
+    hipLaunchKernelGGL(k_dgf_in, dim3(Mpad), dim3(ROW_THREADS), 0, s, feat, static_cast<const uint16_t *>(embed), t, n, d,
                        Mpad / 16, xf, xe);
     return hipGetLastError();
 }
@@ -2838,21 +2274,21 @@ hipError_t launch_dgf_in(const float *feat, const void *embed, const DgfTokens &
 hipError_t launch_dgf_gate_in(const float *h1, const float *h2, int n, int Mpad, int d, uint16_t *xg, hipStream_t s)
 {
     if (n < 1 || n > Mpad || Mpad > DV_TREE_MAX || Mpad % 16 || d % 32) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_dgf_gate_in, dim3(Mpad), dim3(PF_THREADS), 0, s, h1, h2, n, d, Mpad / 16, xg);
+    hipLaunchKernelGGL(k_dgf_gate_in, dim3(Mpad), dim3(ROW_THREADS), 0, s, h1, h2, n, d, Mpad / 16, xg);
     return hipGetLastError();
 }
 
 hipError_t launch_dgf_mix(const float *z, const float *h1, const float *h2, int n, int d, float *x0, hipStream_t s)
 {
     if (n < 1 || n > DV_TREE_MAX) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_dgf_mix, dim3(n), dim3(PF_THREADS), 0, s, z, h1, h2, d, x0);
+    hipLaunchKernelGGL(k_dgf_mix, dim3(n), dim3(ROW_THREADS), 0, s, z, h1, h2, d, x0);
     return hipGetLastError();
 }
 
 hipError_t launch_gather_rows(const float *src, const RowIndex &ix, int n, int d, float *dst, hipStream_t s)
 {
     if (n < 1 || n > DV_TREE_MAX || d % 4) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_gather_rows, dim3(n), dim3(PF_THREADS), 0, s, src, ix, d, dst);
+    hipLaunchKernelGGL(k_gather_rows, dim3(n), dim3(ROW_THREADS), 0, s, src, ix, d, dst);
     return hipGetLastError();
 }
 

@@ -28,7 +28,8 @@ import statistics
 import sys
 
 PKG = os.path.dirname(os.path.abspath(__file__))
-KERNEL_SOURCES = ("csrc/dv_kernels.hip", "csrc/dv_engine.cpp", "csrc/dv_internal.h")
+KERNEL_SOURCES = ("csrc/dv_kernels.hip", "csrc/dv_prefill.hip", "csrc/dv_engine.cpp", "csrc/dv_device.h",
+                  "csrc/dv_internal.h")
 PROJ_PREFIXES = ("k_proj", "k_gemm")
 REF_KERNEL = "k_pack_blocks"
 CLOCK_HZ = 2.4e9      # peak engine clock

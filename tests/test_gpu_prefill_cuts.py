@@ -1,0 +1,65 @@
+"""Prefill at the sizes where the prefill GEMM is cut differently: one token
+group and several (even and uneven), one K range and several, row tiles that
+end early, the smallest chunk (a prompt just above a small max_tree, and the
+one-token rest of a 1025-token prompt), bf16 and int8 weights, on an empty and
+on a cached prefix.  Bars as in test_gpu_prefill.py, whose oracle comparison
+this reuses."""
+import numpy as np
+import pytest
+
+import synth
+from oracle import verify as ov
+from tests.helpers import GpuCase, small_cfg
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("needs a GPU", allow_module_level=True)
+
+from paper_2412_18934_amd import dv  # noqa: E402
+from tests.test_gpu_prefill import _check_next, _check_rows  # noqa: E402
+
+
+def _case(dtype, d, heads, ffn, capacity, max_tree=64):
+    cfg = small_cfg(n_layers=2, d_model=d, n_heads=heads, head_dim=d // heads, d_ffn=ffn, vocab=2048,
+                    weight_dtype=dtype, init_std=0.09 * np.sqrt(256.0 / d))
+    return GpuCase(cfg, seed=501, capacity=capacity, max_tree=max_tree)
+
+
+def _check(case, n, p0, seed):
+    kv = case.new_kv(fill=float("nan"))
+    kv_o = case.synthetic_context(kv, seed, p0)
+    prompt = synth.prompt(seed + 1, n, case.cfg.vocab)
+    ref_kv, logits = ov.prefill(case.w.oracle(), prompt, kv=kv_o)
+    nxt = dv.dv_prefill(case.h, prompt, kv.c)
+    torch.cuda.synchronize()
+    assert kv.len == p0 + n
+    _check_rows(case, kv, ref_kv, p0, n)
+    _check_next(nxt, logits[-1])
+    first = [kv.layer_host(l, p0 + n) for l in range(case.cfg.n_layers)]
+    kv.c.len = p0
+    assert dv.dv_prefill(case.h, prompt, kv.c) == nxt
+    for l, (k, v) in enumerate(first):
+        k2, v2 = kv.layer_host(l, p0 + n)
+        assert np.array_equal(k, k2) and np.array_equal(v, v2)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "i8"])
+@pytest.mark.parametrize("n,p0", [(65, 0), (97, 40), (130, 0), (200, 33), (500, 0), (1025, 7)])
+def test_prefill_cuts(dtype, n, p0):
+    case = _case(dtype, 1024, 8, 2816, 32 * -(-(n + p0) // 32))
+    try:
+        _check(case, n, p0, 5100 + n)
+    finally:
+        case.close()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "i8"])
+@pytest.mark.parametrize("n", [3, 17, 40])
+def test_prefill_small_max_tree(dtype, n):
+    case = _case(dtype, 320, 5, 832, 64, max_tree=2)   # 320: row tiles end early
+    try:
+        _check(case, n, 5, 5300 + n)
+    finally:
+        case.close()
