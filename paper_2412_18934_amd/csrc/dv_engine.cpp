@@ -69,7 +69,7 @@ struct dv_handle {
     const float *lm_scale = nullptr;
     float *ps_lm = nullptr;
     StepDesc *h_sd = nullptr;  // the step's tree (kernels get it by value)
-    DevAccept *d_acc = nullptr, *h_acc = nullptr;
+    DevAccept *d_acc = nullptr, *h_acc = nullptr;  // one pinned host struct, as the device and the host address it
     float *logits_ws = nullptr;  // [max_tree][vocab] logits of a sampled step without out_logits
     // large-M prefill (allocated at its first use, sized for pf_cap tokens,
     // a multiple of 128; pf_part and pf_cnt for the split-K units of any
@@ -435,6 +435,7 @@ int enqueue_forward(dv_handle *h, const dv_kv *kv, float *out_logits, bool with_
     std::memcpy(ac.tokens, sd->tokens, sizeof ac.tokens);
     std::memcpy(ac.parents, sd->parents, sizeof ac.parents);
     std::memcpy(ac.depth, sd->depth, sizeof ac.depth);
+    std::memcpy(ac.anc, sd->anc, sizeof ac.anc);
     ac.acc = h->d_acc;
     prof_begin(h, DV_K_OTHER);
     hipError_t e = launch_accept(ac, s);
@@ -492,6 +493,19 @@ int prepare_sampled(dv_handle *h, const int32_t *tokens, const int32_t *parents,
     }
     sa->acc = acc;
     return DV_OK;
+}
+
+// The walk over the nodes' answers (sample_by_node): from the root along the
+// accepted children; the bonus is the last node's.
+void walk_sampled(DevAccept *a)
+{
+    int32_t path[DV_TREE_MAX], n = 0;
+    for (int node = 0; node >= 0; node = a->path[node]) {
+        path[n++] = node;
+        a->bonus = a->argmax[node];
+    }
+    a->accept_len = n;
+    std::memcpy(a->path, path, n * sizeof(int32_t));
 }
 
 // Large-M prefill: chunks of up to DV_PF_CHUNK tokens, each one causal pass
@@ -680,12 +694,12 @@ int prefill_large(dv_handle *h, const int32_t *tokens, int n, dv_kv *kv, int32_t
             ac.Mpad = 16;
             ac.parents[0] = -1;
             ac.depth[0] = 1;
+            ac.anc[0] = 1;
             ac.acc = h->d_acc;
             prof_begin(h, DV_K_OTHER);
             rc = ck(launch_accept(ac, s), "prefill argmax");
             prof_end(h);
             if (rc) return rc;
-            HIPCHK(h, hipMemcpyAsync(h->h_acc, h->d_acc, sizeof(DevAccept), hipMemcpyDeviceToHost, s));
         }
         HIPCHK(h, hipStreamSynchronize(s));  // also keeps the token upload alive until used
         prof_collect(h);
@@ -931,11 +945,11 @@ int dv_verify_init(const dv_config *cfg, const dv_weights *w, void *stream, dv_h
               dalloc((void **)&h->arg_idx, (size_t)h->p_lm.n_groups * rows * 4) &&
               dalloc((void **)&h->rope_cos, (size_t)c.max_ctx * (hd / 2) * 4) &&
               dalloc((void **)&h->rope_sin, (size_t)c.max_ctx * (hd / 2) * 4) &&
-              dalloc((void **)&h->d_acc, sizeof(DevAccept)) &&
               dalloc((void **)&h->logits_ws, (size_t)c.max_tree * c.vocab * 4) &&
               dalloc((void **)&h->p_ws, (size_t)2 * c.vocab * 4);
     h->h_sd = new StepDesc();
-    ok = ok && hipHostMalloc((void **)&h->h_acc, sizeof(DevAccept), hipHostMallocDefault) == hipSuccess;
+    ok = ok && hipHostMalloc((void **)&h->h_acc, sizeof(DevAccept), hipHostMallocMapped | hipHostMallocCoherent) == hipSuccess &&
+         hipHostGetDevicePointer((void **)&h->d_acc, h->h_acc, 0) == hipSuccess;
     if (!ok) {
         std::string msg = std::string("workspace allocation failed: ") + hipGetErrorString(hipGetLastError());
         dv_verify_free(h);
@@ -1060,10 +1074,10 @@ static int verify_step_impl(dv_handle *h, const int32_t *tokens, const int32_t *
 
     fill_desc(h->h_sd, tokens, tree_parents, n_tree, kv->len, pos, depth, anc);
     if ((rc = enqueue_forward(h, kv, out_logits, true, sampled ? &sa : nullptr))) return rc;
-    HIPCHK(h, hipMemcpyAsync(h->h_acc, h->d_acc, sizeof(DevAccept), hipMemcpyDeviceToHost, h->stream));
     HIPCHK(h, hipStreamSynchronize(h->stream));
     prof_collect(h);
 
+    if (sampled && sample_by_node(h->cfg.vocab)) walk_sampled(h->h_acc);
     const DevAccept &a = *h->h_acc;
     std::memset(out_accept, 0, sizeof *out_accept);
     out_accept->accept_len = a.accept_len;
@@ -1124,9 +1138,9 @@ int dv_accept_sampled(dv_handle *h, const float *logits, const int32_t *tokens, 
     hipError_t e = launch_accept_sampled(sa, h->stream);
     prof_end(h);
     if (e != hipSuccess) return hip_fail(h, e, "sampled accept launch");
-    HIPCHK(h, hipMemcpyAsync(h->h_acc, h->d_acc, sizeof(DevAccept), hipMemcpyDeviceToHost, h->stream));
     HIPCHK(h, hipStreamSynchronize(h->stream));
     prof_collect(h);
+    if (sample_by_node(h->cfg.vocab)) walk_sampled(h->h_acc);
     const DevAccept &a = *h->h_acc;
     std::memset(out_accept, 0, sizeof *out_accept);
     out_accept->accept_len = a.accept_len;
@@ -1174,6 +1188,7 @@ int dv_accept_sampled_noalloc(const float *logits, const int32_t *tokens, const 
     if ((e = hipMemcpyAsync(&a, ws, sizeof a, hipMemcpyDeviceToHost, s)) != hipSuccess ||
         (e = hipStreamSynchronize(s)) != hipSuccess)
         return set_err(nullptr, DV_EHIP, "sampled accept result: %s", hipGetErrorString(e));
+    if (sample_by_node(vocab)) walk_sampled(&a);
     std::memset(out_accept, 0, sizeof *out_accept);
     out_accept->accept_len = a.accept_len;
     out_accept->bonus_token = a.bonus;
@@ -1469,7 +1484,6 @@ int dv_prefill(dv_handle *h, const int32_t *tokens, int32_t n, dv_kv *kv, int32_
         if ((rc = check_tree(h, parents, c, kv->len, pos, depth, anc))) return rc;
         fill_desc(h->h_sd, tokens + done, parents, c, kv->len, pos, depth, anc);
         if ((rc = enqueue_forward(h, kv, nullptr, last))) return rc;
-        if (last) HIPCHK(h, hipMemcpyAsync(h->h_acc, h->d_acc, sizeof(DevAccept), hipMemcpyDeviceToHost, h->stream));
         HIPCHK(h, hipStreamSynchronize(h->stream));
         prof_collect(h);
         kv->len += c;  // a chain's nodes already sit at slots len + k
@@ -1489,7 +1503,7 @@ void dv_verify_free(dv_handle *h)
                     (void *)h->u_s, (void *)h->attn_s, (void *)h->h_s, (void *)h->ssq,
                     (void *)h->part_o, (void *)h->part_m, (void *)h->part_l, (void *)h->attn_cnt, (void *)h->part_gemm, (void *)h->cnt,
                     (void *)h->arg_val, (void *)h->arg_idx, (void *)h->rope_cos,
-                    (void *)h->rope_sin, (void *)h->d_acc, (void *)h->logits_ws, (void *)h->p_ws})
+                    (void *)h->rope_sin, (void *)h->logits_ws, (void *)h->p_ws})
         if (p) (void)hipFree(p);
     for (auto &w : h->layers)
         for (void *p : {(void *)w.pk_qkv, (void *)w.pk_o, (void *)w.pk_gu, (void *)w.pk_down, (void *)w.ps_qkv,

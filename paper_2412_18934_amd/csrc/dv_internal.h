@@ -34,7 +34,8 @@ struct TreeMask {
     uint64_t anc[DV_TREE_MAX];
 };
 
-// Result written by the acceptance kernel, copied back to the host.
+// Result written by the acceptance kernels, for a handle straight into pinned
+// host memory (a device buffer and its copy cost one more launch per step).
 struct DevAccept {
     int32_t accept_len;
     int32_t bonus;
@@ -172,15 +173,20 @@ struct AcceptArgs {
     int32_t n_parts;
     int32_t M, Mpad;
     int32_t tokens[DV_TREE_MAX], parents[DV_TREE_MAX], depth[DV_TREE_MAX];
+    uint64_t anc[DV_TREE_MAX];  // ancestor-or-self masks
     DevAccept *acc;
 };
 
-// Sampled acceptance (one workgroup): the tree walk of the speculative
-// sampling rule over full-vocabulary rows of logits and draft probabilities.
+// Sampled acceptance: the speculative sampling rule over full-vocabulary rows
+// of logits and draft probabilities.  Up to this vocabulary (a row in one
+// workgroup's registers) every node is answered by itself, in acc->path
+// (accepted child or -1) and acc->argmax (bonus), and the host walks the
+// answers; above it one workgroup walks the tree and writes the result.
+constexpr bool sample_by_node(int V) { return V <= 65536; }
 struct SampleArgs {
     const float *logits;       // [M][V]
     const float *q;            // [M][V] draft distributions
-    float *p;                  // [V] workspace: the current (residual) distribution
+    float *p;                  // [2][V] workspace of the one-workgroup walk
     int32_t V, M;
     float inv_t;               // 1 / temperature
     int32_t tokens[DV_TREE_MAX], parents[DV_TREE_MAX];
