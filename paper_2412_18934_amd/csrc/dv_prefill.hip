@@ -65,8 +65,8 @@ __global__ __launch_bounds__(PF_THREADS) void k_pf_embed(const int32_t *tokens, 
 // share one lead of LEAD steps (activations first in each step's loads); the
 // slab is stashed one step ahead into two LDS buffers.
 //
-// The K groups' sums are added through LDS, the KS ranges' through memory:
-// every unit publishes its partial sums (device-coherent stores, completed
+// The K groups' sums are added through LDS, each group taking a share of the
+// token tiles, the KS ranges' through memory: every unit publishes its partial sums (device-coherent stores, completed
 // before it counts itself), and the unit of a tile that counts last adds them
 // in range order and runs the epilogue, so every sum has a fixed order and no
 // workgroup waits for another.
@@ -78,7 +78,11 @@ __global__ __launch_bounds__(64 * NWR * NKG) void k_pf_gemm(PfArgs a)
     // k-steps), XL of them staged per thread of the K group
     constexpr int XE = SK * TT * 128, XL = (XE + GT - 1) / GT;
     static_assert(NT == 512 && LEAD >= 2, "8 waves; the stash needs its loads a step earlier");
-    __shared__ u32x4 xsm[NKG * 2 * XE];
+    constexpr int TI = (TT + NKG - 1) / NKG;  // token tiles per K group after the sums
+    // blocks of the K groups' sums exchanged at a time, as LDS allows
+    constexpr int HB = TT * (NKG - 1) * NWR * BW <= 150 ? BW : 2;
+    constexpr int XN = NKG * 2 * XE, RN = TT * (NKG - 1) * NWR * HB * 64;
+    __shared__ u32x4 xsm[XN > RN ? XN : RN];
     __shared__ float rinv_s[16 * TT];
     __shared__ int last_s;
     // the wave number is the same in all lanes, which the compiler cannot see:
@@ -132,11 +136,11 @@ __global__ __launch_bounds__(64 * NWR * NKG) void k_pf_gemm(PfArgs a)
         for (int i = 0; i < XL; ++i)
             if (XE % GT == 0 || gt + GT * i < XE) slab[buf * XE + gt + GT * i] = stg[j][i];
     };
-    f32x4 acc[BW][TT];
+    f32x4 acc[TT][BW];
 #pragma unroll
-    for (int b = 0; b < BW; ++b)
+    for (int t = 0; t < TT; ++t)
 #pragma unroll
-        for (int t = 0; t < TT; ++t) acc[b][t] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        for (int b = 0; b < BW; ++b) acc[t][b] = (f32x4){0.f, 0.f, 0.f, 0.f};
     // a step held in register slot j: the B operands of tile and k-step q + 1
     // are read while the MFMAs of q run (the scheduling barriers keep the
     // compiler from moving the reads down to their use, where every tile's
@@ -168,9 +172,9 @@ __global__ __launch_bounds__(64 * NWR * NKG) void k_pf_gemm(PfArgs a)
                 }
             }
 #pragma unroll
-            for (int b = 0; b < BW; ++b) acc[b][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[b], hi, acc[b][t], 0, 0, 0);
+            for (int b = 0; b < BW; ++b) acc[t][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[b], hi, acc[t][b], 0, 0, 0);
 #pragma unroll
-            for (int b = 0; b < BW; ++b) acc[b][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[b], lo, acc[b][t], 0, 0, 0);
+            for (int b = 0; b < BW; ++b) acc[t][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[b], lo, acc[t][b], 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
         }
     };
@@ -211,44 +215,70 @@ __global__ __launch_bounds__(64 * NWR * NKG) void k_pf_gemm(PfArgs a)
             __syncthreads();
         }
     }
-    // K groups -> group 0, in order, HB blocks at a time through the slabs' LDS
-    if constexpr (NKG > 1) {
-        constexpr int HB = NKG == 2 ? 2 : 4;
-        static_assert(NWR * HB * TT * 64 <= NKG * 2 * XE, "the sums of one K group's waves fit the slabs");
+    // The K groups share what follows by token tiles: group kg ends up with the
+    // tiles kg, kg + NKG, ... (own[i] = tile kg + NKG i), so that all waves
+    // sum, fold and run the epilogue.
+    const int cnt_t = full ? TT : TT - 1;
+    f32x4 own[TI][BW];
+    if constexpr (NKG == 1) {
 #pragma unroll
-        for (int q = 1; q < NKG; ++q)
+        for (int t = 0; t < TT; ++t)
 #pragma unroll
-            for (int b0 = 0; b0 < BW; b0 += HB) {
-                if (kg == q) {
+            for (int b = 0; b < BW; ++b) own[t][b] = acc[t][b];
+    } else {
+        // through LDS, HB blocks at a time: a wave leaves the tiles of the
+        // other groups there and adds theirs to its own, in group order
+#pragma unroll
+        for (int b0 = 0; b0 < BW; b0 += HB) {
+            if (b0) __syncthreads();
+#pragma unroll
+            for (int t = 0; t < TT; ++t) {
+                if (t % NKG == kg) {
+#pragma unroll
+                    for (int b = 0; b < HB; ++b) own[t / NKG][b0 + b] = acc[t][b0 + b];
+                } else {
+                    const int r = kg < t % NKG ? kg : kg - 1;
 #pragma unroll
                     for (int b = 0; b < HB; ++b)
-#pragma unroll
-                        for (int t = 0; t < TT; ++t)
-                            xsm[((wr * HB + b) * TT + t) * 64 + lane] = __builtin_bit_cast(u32x4, acc[b0 + b][t]);
+                        xsm[(((t * (NKG - 1) + r) * NWR + wr) * HB + b) * 64 + lane] =
+                            __builtin_bit_cast(u32x4, acc[t][b0 + b]);
                 }
-                __syncthreads();
-                if (kg == 0) {
-#pragma unroll
-                    for (int b = 0; b < HB; ++b)
-#pragma unroll
-                        for (int t = 0; t < TT; ++t)
-                            acc[b0 + b][t] += __builtin_bit_cast(f32x4, xsm[((wr * HB + b) * TT + t) * 64 + lane]);
-                }
-                __syncthreads();
             }
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < TI; ++i) {
+                const int t = min(kg + NKG * i, TT - 1);
+                f32x4 sum[HB];
+#pragma unroll
+                for (int b = 0; b < HB; ++b) sum[b] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int q = 0; q < NKG; ++q) {
+                    const int r = q < kg ? q : q - 1;
+#pragma unroll
+                    for (int b = 0; b < HB; ++b)
+                        sum[b] += q == kg ? own[i][b0 + b]
+                                          : __builtin_bit_cast(f32x4, xsm[(((t * (NKG - 1) + r) * NWR + wr) * HB + b) * 64 + lane]);
+                }
+#pragma unroll
+                for (int b = 0; b < HB; ++b) own[i][b0 + b] = sum[b];
+            }
+        }
     }
     if (KS > 1) {
         constexpr int PW = NWR * BW * TT * 64;  // 16-byte partials of a unit
         const __amdgpu_buffer_rsrc_t pr = rsrc_of(a.part);
-        auto pofs = [&](int u, int b, int t) -> uint32_t { return (uint32_t)(u * PW + ((b * TT + t) * NWR + wr) * 64 + lane) * 16u; };
-        if (kg == 0) {
+        auto pofs = [&](int u, int t, int b) -> uint32_t {
+            return (uint32_t)(u * PW + ((t * BW + b) * NWR + wr) * 64 + lane) * 16u;
+        };
+#pragma unroll
+        for (int i = 0; i < TI; ++i) {
+            if (kg + NKG * i >= cnt_t) break;
 #pragma unroll
             for (int b = 0; b < BW; ++b)
-#pragma unroll
-                for (int t = 0; t < TT; ++t)
-                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[b][t]), pr, pofs(unit, b, t), 0, 16);
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, own[i][b]), pr,
+                                                       pofs(unit, kg + NKG * i, b), 0, 16);
         }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         if (tid == 0) {
             uint32_t *cnt = a.cnt + rtile * n_tt + tg;
@@ -257,41 +287,42 @@ __global__ __launch_bounds__(64 * NWR * NKG) void k_pf_gemm(PfArgs a)
             if (old == (uint32_t)(KS - 1)) __hip_atomic_store(cnt, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         __syncthreads();
-        if (!last_s || kg != 0) return;
-        // ranges in order, two ranges of one block in flight together
+        if (!last_s) return;
+        // ranges in order, KB ranges of a tile in flight together
+        constexpr int KB = 4;
         const int u0 = rtile * KS * n_tt + tg;
 #pragma unroll
-        for (int b = 0; b < BW; ++b) {
-            f32x4 sum[TT];
+        for (int i = 0; i < TI; ++i) {
+            const int t = min(kg + NKG * i, cnt_t - 1);
+            f32x4 sum[BW];
 #pragma unroll
-            for (int t = 0; t < TT; ++t) sum[t] = (f32x4){0.f, 0.f, 0.f, 0.f};
-            for (int k0 = 0; k0 < KS; k0 += 2) {
-                u32x4 raw[2][TT];
+            for (int b = 0; b < BW; ++b) sum[b] = (f32x4){0.f, 0.f, 0.f, 0.f};
+            for (int k0 = 0; k0 < KS; k0 += KB) {
+                u32x4 raw[KB][BW];
 #pragma unroll
-                for (int q = 0; q < 2; ++q)
+                for (int q = 0; q < KB; ++q)
 #pragma unroll
-                    for (int t = 0; t < TT; ++t)
-                        raw[q][t] = __builtin_amdgcn_raw_buffer_load_b128(pr, pofs(u0 + min(k0 + q, KS - 1) * n_tt, b, t), 0, 16);
+                    for (int b = 0; b < BW; ++b)
+                        raw[q][b] = __builtin_amdgcn_raw_buffer_load_b128(pr, pofs(u0 + min(k0 + q, KS - 1) * n_tt, t, b), 0, 16);
 #pragma unroll
-                for (int q = 0; q < 2; ++q) {
+                for (int q = 0; q < KB; ++q) {
                     if (k0 + q < KS) {
 #pragma unroll
-                        for (int t = 0; t < TT; ++t) sum[t] += __builtin_bit_cast(f32x4, raw[q][t]);
+                        for (int b = 0; b < BW; ++b) sum[b] += __builtin_bit_cast(f32x4, raw[q][b]);
                     }
                 }
             }
 #pragma unroll
-            for (int t = 0; t < TT; ++t) acc[b][t] = sum[t];
+            for (int b = 0; b < BW; ++b) own[i][b] = sum[b];
         }
     }
-    if (kg != 0) return;
     if constexpr (Q8) {
         // W = scale[row] q
 #pragma unroll
         for (int b = 0; b < BW; ++b) {
             const f32x4 rs = *reinterpret_cast<const f32x4 *>(a.scale + min(gb0 + b, a.NB - 1) * 16 + 4 * (lane >> 4));
 #pragma unroll
-            for (int t = 0; t < TT; ++t) acc[b][t] *= rs;
+            for (int i = 0; i < TI; ++i) own[i][b] *= rs;
         }
     }
 
@@ -307,16 +338,17 @@ __global__ __launch_bounds__(64 * NWR * NKG) void k_pf_gemm(PfArgs a)
             const int tile = gb >> 1, seg = tile / per_seg, tt = tile - seg * per_seg;
             const int h = tt / per_head, j0 = (tt - h * per_head) * 16 + r4;
 #pragma unroll
-            for (int t = 0; t < TT; ++t) {
-                if (t == TT - 1 && !full) break;
+            for (int i = 0; i < TI; ++i) {
+                const int t = kg + NKG * i;
+                if (t >= cnt_t) break;
                 const int ml = t * 16 + n16, m = tt0 * 16 + ml;
                 if (m >= a.M) continue;
                 const float ri = rinv_s[ml];
                 float y1[4], y2[4];
 #pragma unroll
                 for (int jj = 0; jj < 4; ++jj) {
-                    y1[jj] = acc[2 * p][t][jj] * ri;
-                    y2[jj] = acc[2 * p + 1][t][jj] * ri;
+                    y1[jj] = own[i][2 * p][jj] * ri;
+                    y2[jj] = own[i][2 * p + 1][jj] * ri;
                 }
                 const int pos = a.P0 + m;
                 if (seg < 2) {
@@ -357,14 +389,15 @@ __global__ __launch_bounds__(64 * NWR * NKG) void k_pf_gemm(PfArgs a)
             if (gb >= a.NB) break;
             const int f0 = 16 * (gb >> 1) + r4;
 #pragma unroll
-            for (int t = 0; t < TT; ++t) {
-                if (t == TT - 1 && !full) break;  // a group of TT - 1 tiles
+            for (int i = 0; i < TI; ++i) {
+                const int t = kg + NKG * i;
+                if (t >= cnt_t) break;
                 const int ml = t * 16 + n16, m = tt0 * 16 + ml;
                 float hv[4] = {0.f, 0.f, 0.f, 0.f};
                 if (m < a.M) {
                     const float ri = rinv_s[ml];
 #pragma unroll
-                    for (int jj = 0; jj < 4; ++jj) hv[jj] = silu(acc[2 * p][t][jj] * ri) * (acc[2 * p + 1][t][jj] * ri);
+                    for (int jj = 0; jj < 4; ++jj) hv[jj] = silu(own[i][2 * p][jj] * ri) * (own[i][2 * p + 1][jj] * ri);
                 }
                 store_split4(a.hs, m, f0, a.MT, make_float4(hv[0], hv[1], hv[2], hv[3]));
             }
@@ -373,8 +406,9 @@ __global__ __launch_bounds__(64 * NWR * NKG) void k_pf_gemm(PfArgs a)
         if (gb0 < a.NB) {
             const int nsq = a.d / 64;
 #pragma unroll
-            for (int t = 0; t < TT; ++t) {
-                if (t == TT - 1 && !full) break;  // a group of TT - 1 tiles (wave-uniform)
+            for (int i = 0; i < TI; ++i) {
+                const int t = kg + NKG * i;
+                if (t >= cnt_t) break;
                 const int ml = t * 16 + n16, m = tt0 * 16 + ml;
                 float ss = 0.f;
 #pragma unroll
@@ -384,10 +418,10 @@ __global__ __launch_bounds__(64 * NWR * NKG) void k_pf_gemm(PfArgs a)
                     if (m < a.M) {
                         float *xp = a.x + (size_t)m * a.d + r;
                         xv = *reinterpret_cast<const float4 *>(xp);
-                        xv.x += acc[b][t][0];
-                        xv.y += acc[b][t][1];
-                        xv.z += acc[b][t][2];
-                        xv.w += acc[b][t][3];
+                        xv.x += own[i][b][0];
+                        xv.y += own[i][b][1];
+                        xv.z += own[i][b][2];
+                        xv.w += own[i][b][3];
                         *reinterpret_cast<float4 *>(xp) = xv;
                     }
                     ss = fmaf(xv.x, xv.x, fmaf(xv.y, xv.y, fmaf(xv.z, xv.z, fmaf(xv.w, xv.w, ss))));
@@ -646,12 +680,13 @@ hipError_t pf_launch_epi(const PfArgs &a, int shape, int tt, hipStream_t s)
 // per KB of partials the folding unit reads and g us per MB that all units
 // write.  Small row counts and short prompts need K ranges or K groups to reach
 // every CU; large ones lose to them by the partials' traffic.  The constants
-// are a fit to 2700 launches on random data at (d_model, d_ffn) = (4096,
+// are a fit to 2900 launches on random data at (d_model, d_ffn) = (4096,
 // 11008) and (5120, 13824), 5 to 64 token tiles, every cut: the chosen one is
-// 1% slower than the fastest on average, 9% at most (int8: 17%).  Before, 512 x
+// 1% slower than the fastest on average, 6% at most.  Before, 512 x
 // 128 (QKV, gate/up) and 512 x 48 tiles (O, down) ran over all of K, with the
-// B operands read just before use.  160 tokens, 7B width, us: QKV 168 -> 52,
-// O 84 -> 38, gate/up 170 -> 76, down 206 -> 57; 1024 tokens, 13B width,
+// B operands read just before use.  160 tokens, 7B width, us: QKV 168 -> 50,
+// O 84 -> 30, gate/up 170 -> 75, down 206 -> 49 (38 and 57 for O and down while
+// one K group's waves did all sums, folds and epilogues); 1024 tokens, 13B width,
 // inside the model: 248 -> 245, 125 -> 116, 473 -> 454, 302 -> 255.
 //
 // min_parts: the least number of parts (K groups x ranges) a sum is added from.
@@ -664,9 +699,9 @@ PfPlan pf_plan(int NB, int MT, int K, bool q8, int min_parts, int n_cu)
     struct Fit {
         double a, b, c;
     };
-    static const Fit fit[2][3] = {{{0.306, 0.114, 1.3}, {0.247, 0.150, 7.2}, {0.292, 0.191, 9.9}},
-                                  {{0.561, 0.257, 0.8}, {0.214, 0.359, 5.4}, {0, 0, 0}}};
-    const double e = q8 ? 13.3 : 11.5, f = q8 ? 0.018 : 0.019, g = q8 ? 0.23 : 0.30;
+    static const Fit fit[2][3] = {{{0.236, 0.126, 5.5}, {0.265, 0.147, 6.1}, {0.389, 0.170, 6.8}},
+                                  {{0.492, 0.271, 3.2}, {0.365, 0.334, 3.2}, {0, 0, 0}}};
+    const double e = q8 ? 10.3 : 7.7, f = q8 ? 0.017 : 0.018, g = q8 ? 0.26 : 0.33;
     // Where every CU is kept busy the chip's power sets the rate, not the cut:
     // 27648 x 5120 at 1024 tokens takes 424 us as 432 units (84% of two rounds)
     // and 434-466 us as 486 (95%).  Cuts below that time count as equal and the
