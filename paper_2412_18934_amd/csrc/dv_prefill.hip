@@ -448,8 +448,17 @@ __global__ __launch_bounds__(64 * NWR * NKG) void k_pf_gemm(PfArgs a)
 // layout of MT token tiles).  Grid (heads, query blocks) with the last query
 // block first: workgroups are dispatched in order, so the longest ones (the
 // most keys) start first and the short ones fill in behind them.
-template <int HD>
-__global__ __launch_bounds__(256) void k_attn_causal(const float *q, const uint16_t *kc_l, const uint16_t *vc_l,
+//
+// A wave's tiles are a serial chain of about 1.3 us each, so with few query
+// blocks (short prompts) the workgroup takes NKG key groups of 4 waves: group
+// kg has the tiles kg, kg + NKG, ..., each group stages its own, and the
+// groups' outputs are combined through LDS in group order.  One group and two,
+// us (and before the wave number and the tile loads' bounds were made uniform):
+// 7B heads, 150 queries behind 333 keys 24.7, 19.6 (26.5); 13B heads, 136
+// behind 1839 80, 61 (88); 500 alone 32.5, 26.9 (34.6); 1024 alone 56.7, 60
+// (60.9).
+template <int HD, int NKG>
+__global__ __launch_bounds__(256 * NKG) void k_attn_causal(const float *q, const uint16_t *kc_l, const uint16_t *vc_l,
                                                      int M, int P0, int H, int cap, int MT, uint16_t *out)
 {
     constexpr int NC = HD / 32, ND = HD / 16;
@@ -458,8 +467,14 @@ __global__ __launch_bounds__(256) void k_attn_causal(const float *q, const uint1
     constexpr int KBYTES = 32 * KROW, VBYTES = HD * VROW;
     constexpr int KCH = 32 * HD / 8, VCH = HD * 4;  // 16-byte chunks of a tile's K and V
     constexpr int CPT = (KCH + VCH + 255) / 256;     // chunks per thread
-    __shared__ __align__(16) unsigned char smem[2][KBYTES + VBYTES];
-    const int h = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    constexpr int STG = 2 * (KBYTES + VBYTES);       // a key group's two buffers
+    constexpr int OROW = HD + 4, OBYTES = NKG > 1 ? (NKG - 1) * 64 * OROW * 4 : 0;  // combined outputs
+    __shared__ __align__(16) unsigned char smem_all[NKG * STG > OBYTES ? NKG * STG : OBYTES];
+    __shared__ float sm_m[NKG][64], sm_l[NKG][64];
+    // (uniform in a wave, said so for scalar addresses and branches)
+    const int kg = NKG == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
+    unsigned char *const smem_g = smem_all + kg * STG;
+    const int h = blockIdx.x, tid = threadIdx.x & 255, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 15, g = lane >> 4;
     const int q0 = (gridDim.y - 1 - blockIdx.y) * 64;
     const int qb = q0 + wave * 16;               // first query of this wave
@@ -503,13 +518,14 @@ __global__ __launch_bounds__(256) void k_attn_causal(const float *q, const uint1
     auto stash = [&](int buf) {
 #pragma unroll
         for (int i = 0; i < CPT; ++i) {
+            unsigned char *const sm = smem_g + buf * (KBYTES + VBYTES);
             const int e = tid + 256 * i;
             if (e < KCH) {
                 const int r = e / (HD / 8), c8 = e % (HD / 8);
-                *reinterpret_cast<u32x4 *>(&smem[buf][r * KROW + 16 * c8]) = stg[i];
+                *reinterpret_cast<u32x4 *>(sm + r * KROW + 16 * c8) = stg[i];
             } else if (e < KCH + VCH) {
                 const int ev = e - KCH, dr = ev >> 2, c8 = ev & 3;
-                *reinterpret_cast<u32x4 *>(&smem[buf][KBYTES + dr * VROW + 16 * c8]) = stg[i];
+                *reinterpret_cast<u32x4 *>(sm + KBYTES + dr * VROW + 16 * c8) = stg[i];
             }
         }
     };
@@ -520,7 +536,7 @@ __global__ __launch_bounds__(256) void k_attn_causal(const float *q, const uint1
     for (int dt = 0; dt < ND; ++dt) o[dt] = (f32x4){0.f, 0.f, 0.f, 0.f};
     auto process = [&](int t, int buf) {
         const int k0 = 32 * t;
-        const unsigned char *ks = smem[buf], *vs = smem[buf] + KBYTES;
+        const unsigned char *ks = smem_g + buf * (KBYTES + VBYTES), *vs = ks + KBYTES;
         const int ra = 8 * (n >> 2) + (n & 3), rb = ra + 4;
         f32x4 sa = (f32x4){0.f, 0.f, 0.f, 0.f}, sb = sa;
 #pragma unroll
@@ -586,15 +602,58 @@ __global__ __launch_bounds__(256) void k_attn_causal(const float *q, const uint1
             o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pl, v8, o[dt], 0, 0, 0);
         }
     };
-    fetch(0);
+    fetch(min(kg, ntile - 1));  // (a group past the last tile repeats it, unused)
     stash(0);
     __syncthreads();
-    for (int t = 0; t < ntile; ++t) {
-        const int buf = t & 1;
-        if (t + 1 < ntile) fetch(t + 1);  // in flight while tile t is used
+    for (int t0 = 0; t0 < ntile; t0 += NKG) {
+        const int t = t0 + kg, buf = (t0 / NKG) & 1;
+        const bool more = t0 + NKG < ntile;
+        if (more) fetch(min(t + NKG, ntile - 1));  // in flight while tile t is used
         if (t < wtiles) process(t, buf);
-        if (t + 1 < ntile) stash(buf ^ 1);
+        if (more) stash(buf ^ 1);
         __syncthreads();
+    }
+    if constexpr (NKG > 1) {
+        // groups 1.. leave their outputs in LDS, group 0 combines them
+        float *const so = reinterpret_cast<float *>(smem_all);
+        if (g == 0) {
+            sm_m[kg][16 * wave + n] = m_run;
+            sm_l[kg][16 * wave + n] = l_run;
+        }
+        if (kg > 0) {
+#pragma unroll
+            for (int dt = 0; dt < ND; ++dt)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    so[((kg - 1) * 64 + 16 * wave + 4 * g + j) * OROW + dt * 16 + n] = o[dt][j];
+        }
+        __syncthreads();
+        if (kg > 0) return;
+        float mx = -INFINITY, l = 0.f;
+#pragma unroll
+        for (int q = 0; q < NKG; ++q) mx = fmaxf(mx, sm_m[q][16 * wave + n]);
+        float wq[NKG];
+#pragma unroll
+        for (int q = 0; q < NKG; ++q) {
+            const float mq = sm_m[q][16 * wave + n];
+            wq[q] = mq == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mq - mx);
+            l = fmaf(wq[q], sm_l[q][16 * wave + n], l);
+        }
+        l_run = l;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            float wj[NKG];
+#pragma unroll
+            for (int q = 0; q < NKG; ++q) wj[q] = __shfl(wq[q], 4 * g + j);
+#pragma unroll
+            for (int dt = 0; dt < ND; ++dt) {
+                float v = o[dt][j] * wj[0];
+#pragma unroll
+                for (int q = 1; q < NKG; ++q)
+                    v = fmaf(wj[q], so[((q - 1) * 64 + 16 * wave + 4 * g + j) * OROW + dt * 16 + n], v);
+                o[dt][j] = v;
+            }
+        }
     }
     if (!active) return;
     // rows of o are queries qb + 4g + j; their sums l sit in lanes 4g + j
@@ -751,13 +810,27 @@ hipError_t launch_pf_gemm(const PfArgs &a, const PfPlan &p, int epi, hipStream_t
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_attn_causal(const float *q, const void *kc, const void *vc, int M, int P0, int H, int hd, int cap,
-                              int MT, uint16_t *out, hipStream_t s)
+template <int HD>
+static hipError_t causal_launch(int nkg, const float *q, const void *kc, const void *vc, int M, int P0, int H, int cap,
+                                int MT, uint16_t *out, hipStream_t s)
 {
     const dim3 grid(H, (M + 63) / 64);
     const uint16_t *k16 = static_cast<const uint16_t *>(kc), *v16 = static_cast<const uint16_t *>(vc);
-    if (hd == 128) hipLaunchKernelGGL(k_attn_causal<128>, grid, dim3(256), 0, s, q, k16, v16, M, P0, H, cap, MT, out);
-    else if (hd == 64) hipLaunchKernelGGL(k_attn_causal<64>, grid, dim3(256), 0, s, q, k16, v16, M, P0, H, cap, MT, out);
-    else return hipErrorInvalidValue;
+    if (nkg == 2) hipLaunchKernelGGL((k_attn_causal<HD, 2>), grid, dim3(512), 0, s, q, k16, v16, M, P0, H, cap, MT, out);
+    else hipLaunchKernelGGL((k_attn_causal<HD, 1>), grid, dim3(256), 0, s, q, k16, v16, M, P0, H, cap, MT, out);
     return hipGetLastError();
+}
+
+hipError_t launch_attn_causal(const float *q, const void *kc, const void *vc, int M, int P0, int H, int hd, int cap,
+                              int MT, uint16_t *out, hipStream_t s)
+{
+    // Two key groups while the query blocks do not fill the CUs, and up to two
+    // workgroups per CU when the prompt is most of the keys (the query blocks
+    // are then uneven and the longest one sets the time); 280 workgroups of 29
+    // to 41 tiles each: 71 us with one group, 75 with two.
+    const int wgs = H * ((M + 63) / 64), tiles = (P0 + M + 31) / 32;
+    const int nkg = tiles >= 4 && (wgs <= 256 || (wgs <= 512 && P0 <= M)) ? 2 : 1;
+    if (hd == 128) return causal_launch<128>(nkg, q, kc, vc, M, P0, H, cap, MT, out, s);
+    if (hd == 64) return causal_launch<64>(nkg, q, kc, vc, M, P0, H, cap, MT, out, s);
+    return hipErrorInvalidValue;
 }

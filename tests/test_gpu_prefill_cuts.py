@@ -63,3 +63,15 @@ def test_prefill_small_max_tree(dtype, n):
         _check(case, n, 5, 5300 + n)
     finally:
         case.close()
+
+
+@pytest.mark.parametrize("heads,n,p0", [(8, 70, 0), (8, 96, 5), (8, 65, 300), (4, 140, 1), (16, 130, 700)])
+def test_prefill_attention_key_groups(heads, n, p0):
+    """Few query blocks: two key groups per workgroup, with odd and even tile
+    counts, a group without a tile for some waves, both head sizes."""
+    case = _case("bf16", 512, heads, 1408, 32 * -(-(n + p0) // 32)) if heads != 16 else \
+        _case("bf16", 1024, heads, 2816, 32 * -(-(n + p0) // 32))
+    try:
+        _check(case, n, p0, 5500 + n)
+    finally:
+        case.close()
