@@ -370,6 +370,38 @@ int enqueue_forward(dv_handle *h, const dv_kv *kv, float *out_logits, bool with_
         return DV_OK;
     };
 
+    // 33 to 64 nodes, bf16 weights: gate/up and lm_head on the prefill GEMM where
+    // pf_for_step finds it faster.  Its workgroups share the activations of 128
+    // rows through LDS; the streaming kernel's waves load them from L2 for
+    // every 64, twice the weight bytes at 64 nodes, and are bound by that.
+    // (O and down stream with K ranges, and few QKV sizes have the rows for it.)
+    auto step_gemm = [&](int epi, const uint16_t *packed, int NB, float *logits) -> int {
+        PfArgs a{};
+        a.packed = packed;
+        a.NB = NB;
+        a.K = d;
+        a.xs = h->u_s;
+        a.MT = mt;
+        a.n_tt = PF_STEP_PLAN.n_tt;
+        a.ks = PF_STEP_PLAN.ks;
+        a.M = M;
+        a.ssq_in = h->ssq;
+        a.nsq_in = g.n_ssq_in;
+        a.eps = c.rms_eps;
+        a.d = d;
+        a.hs = h->h_s;
+        a.logits = logits;
+        a.arg_val = h->arg_val;
+        a.arg_idx = h->arg_idx;
+        prof_begin(h, DV_K_GEMM);
+        const hipError_t e = launch_pf_gemm(a, PF_STEP_PLAN, epi, s);
+        prof_end(h);
+        return e == hipSuccess ? DV_OK : hip_fail(h, e, "step GEMM launch");
+    };
+    const bool pf_step = h->wkind == W_BF16 && d % 64 == 0 && h->p_down.mfma;
+    const bool gu_pf = pf_step && pf_for_step(F / 8, d, mt, h->n_cu);
+    const bool lm_pf = pf_step && pf_for_step(c.vocab / 16, d, mt, h->n_cu);
+
     {
         NormArgs na{};
         na.x = h->x;
@@ -404,9 +436,10 @@ int enqueue_forward(dv_handle *h, const dv_kv *kv, float *out_logits, bool with_
         if ((rc = gemm(h->p_o, EPI_RESID, w.wo, nullptr, nullptr, w.pk_o, w.ps_o, d, d, h->attn, h->attn_s, nullptr,
                        w.ffn_norm)))
             return rc;
-        if ((rc = gemm(h->p_gu, EPI_SWIGLU, w.w_gate, w.w_up, nullptr, w.pk_gu, w.ps_gu, F, d, h->u, h->u_s, h->hbuf,
-                       nullptr)))
-            return rc;
+        rc = gu_pf ? step_gemm(EPI_SWIGLU, w.pk_gu, F / 8, nullptr)
+                   : gemm(h->p_gu, EPI_SWIGLU, w.w_gate, w.w_up, nullptr, w.pk_gu, w.ps_gu, F, d, h->u, h->u_s, h->hbuf,
+                          nullptr);
+        if (rc) return rc;
         const void *next_gain = l + 1 < c.n_layers ? h->layers[l + 1].attn_norm : h->final_norm;
         if ((rc = gemm(h->p_down, EPI_RESID, w.w_down, nullptr, nullptr, w.pk_down, w.ps_down, d, F, h->hbuf, h->h_s,
                        nullptr, next_gain)))
@@ -415,9 +448,10 @@ int enqueue_forward(dv_handle *h, const dv_kv *kv, float *out_logits, bool with_
     if (!with_head) return DV_OK;
     g.arg_val = h->arg_val;
     g.arg_idx = h->arg_idx;
-    if ((rc = gemm(h->p_lm, EPI_LOGITS, h->lm_head, nullptr, nullptr, h->pk_lm, h->ps_lm, c.vocab, d, h->u, h->u_s,
-                   out_logits, nullptr)))
-        return rc;
+    rc = lm_pf ? step_gemm(EPI_LOGITS, h->pk_lm, c.vocab / 16, out_logits)
+               : gemm(h->p_lm, EPI_LOGITS, h->lm_head, nullptr, nullptr, h->pk_lm, h->ps_lm, c.vocab, d, h->u, h->u_s,
+                      out_logits, nullptr);
+    if (rc) return rc;
     if (smp) {
         smp->logits = out_logits;
         prof_begin(h, DV_K_OTHER);
@@ -429,7 +463,8 @@ int enqueue_forward(dv_handle *h, const dv_kv *kv, float *out_logits, bool with_
     AcceptArgs ac{};
     ac.arg_val = h->arg_val;
     ac.arg_idx = h->arg_idx;
-    ac.n_parts = step_plan(h->p_lm, EPI_LOGITS, h->wkind, mt, h->n_cu).n_groups;  // the lm_head launch's groups
+    // the lm_head launch's groups
+    ac.n_parts = lm_pf ? (c.vocab / 16 + 3) / 4 : step_plan(h->p_lm, EPI_LOGITS, h->wkind, mt, h->n_cu).n_groups;
     ac.M = M;
     ac.Mpad = Mpad;
     std::memcpy(ac.tokens, sd->tokens, sizeof ac.tokens);
@@ -518,7 +553,10 @@ bool pf_supported(const dv_handle *h)
 {
     const dv_config &c = h->cfg;
     return h->wkind != W_F32 && h->p_qkv.mfma && h->p_o.mfma && h->p_gu.mfma && h->p_down.mfma &&
-           c.d_model % 64 == 0 && (c.head_dim == 64 || c.head_dim == 128);
+           c.d_model % 64 == 0 && (c.head_dim == 64 || c.head_dim == 128) &&
+           pf_addressable(3 * c.d_model / 16, c.d_model, h->wkind == W_I8) &&
+           pf_addressable(c.d_ffn / 8, c.d_model, h->wkind == W_I8) &&
+           pf_addressable(c.d_model / 16, c.d_ffn, h->wkind == W_I8);
 }
 
 // The workspace is one allocation (a new handle's first prefill pays for it),

@@ -263,6 +263,11 @@ struct PfArgs {
     const float *rope_cos, *rope_sin;
     // SWIGLU: h in split layout (K = F)
     uint16_t *hs;
+    // LOGITS (trees of 33 to 64 nodes): logits [M][16 NB] or null, and the
+    // (max, argmax) of every 64 rows, [M][ceil(NB / 4)]
+    float *logits;
+    float *arg_val;
+    int32_t *arg_idx;
     // RESID: x [Mp][d] += sums; us = x * gain (split layout), ssq_out [Mp][d / 64]
     float *x;
     const uint16_t *gain;
@@ -279,7 +284,25 @@ struct PfPlan {
     int shape, tt, n_tt, ks;
 };
 PfPlan pf_plan(int NB, int MT, int K, bool q8, int min_parts, int n_cu);
-// the prefill GEMM with the EPI_QKV, EPI_SWIGLU or EPI_RESID epilogue
+// the prefill GEMM addresses a matrix with 31-bit byte offsets
+inline bool pf_addressable(int NB, int K, bool q8) { return (double)NB * K * (q8 ? 16 : 32) < 2147483648.0; }
+// Whether a bf16 projection of NB blocks without K splits, over a verify step's
+// mt token tiles, runs on the prefill GEMM (128 rows a workgroup), and its cut
+// there (no K ranges, so no workspace).  The streaming kernel takes 64 rows a
+// workgroup, one workgroup of either per CU: where both need the same number of
+// rounds, or the prefill GEMM more than half as many, the streaming kernel is
+// ahead.  K = 5120, 60 nodes, streaming / prefill, us, by rows / 128 on 256 CUs:
+// 64 (1 round / 1) 38 / 52, 128 (1 / 1) 40 / 54, 136 (2 / 1) 69 / 57, 216
+// (2 / 1) 74 / 61, 250 (2 / 1) 83 / 66, 288 (3 / 2) 109 / 113, 384 (3 / 2) 125 /
+// 121; K = 8192: 448 (4 / 2) 248 / 216, 1002 (8 / 4) 519 / 459.  40 nodes alike.
+inline bool pf_for_step(int NB, int K, int mt, int n_cu)
+{
+    const int stream = (NB / 4 + n_cu - 1) / n_cu, pf = ((NB + 7) / 8 + n_cu - 1) / n_cu;
+    return (mt == 3 || mt == 4) && NB % 4 == 0 && stream == 2 * pf && pf_addressable(NB, K, false);
+}
+constexpr PfPlan PF_STEP_PLAN{2, 4, 1, 1};
+// the prefill GEMM with the EPI_QKV, EPI_SWIGLU or EPI_RESID epilogue, or
+// EPI_LOGITS with PF_STEP_PLAN
 hipError_t launch_pf_gemm(const PfArgs &a, const PfPlan &p, int epi, hipStream_t s);
 // causal attention of the chunk; output in split layout (MT token tiles)
 hipError_t launch_attn_causal(const float *q, const void *kc, const void *vc, int M, int P0, int H, int hd, int cap,

@@ -402,6 +402,58 @@ __global__ __launch_bounds__(64 * NWR * NKG) void k_pf_gemm(PfArgs a)
                 store_split4(a.hs, m, f0, a.MT, make_float4(hv[0], hv[1], hv[2], hv[3]));
             }
         }
+    } else if (EPI == EPI_LOGITS) {
+        if (gb0 < a.NB) {
+            const size_t V = (size_t)a.NB * 16;
+            const int n_parts = (a.NB + 3) / 4;
+            const bool vec = (reinterpret_cast<uintptr_t>(a.logits) & 15) == 0;
+#pragma unroll
+            for (int i = 0; i < TI; ++i) {
+                const int t = kg + NKG * i;
+                if (t >= cnt_t) break;
+                const int ml = t * 16 + n16, m = tt0 * 16 + ml;
+                const float ri = rinv_s[ml];
+                float best = -INFINITY;
+                int bi = 16 * (gb0 + BW);  // as the streaming kernel's where no value compares larger
+#pragma unroll
+                for (int b = 0; b < BW; ++b) {
+                    if (gb0 + b >= a.NB) break;
+                    const int r = 16 * (gb0 + b) + r4;
+                    float v[4];
+#pragma unroll
+                    for (int jj = 0; jj < 4; ++jj) {
+                        v[jj] = own[i][b][jj] * ri;
+                        if (v[jj] > best) {
+                            best = v[jj];
+                            bi = r + jj;
+                        }
+                    }
+                    if (a.logits && m < a.M) {
+                        float *lp = a.logits + m * V + r;
+                        if (vec) {
+                            *reinterpret_cast<float4 *>(lp) = make_float4(v[0], v[1], v[2], v[3]);
+                        } else {
+#pragma unroll
+                            for (int jj = 0; jj < 4; ++jj) lp[jj] = v[jj];
+                        }
+                    }
+                }
+                // larger value, then lower row
+#pragma unroll
+                for (int off = 16; off < 64; off <<= 1) {
+                    const float v2 = __shfl_xor(best, off);
+                    const int i2 = __shfl_xor(bi, off);
+                    if (v2 > best || (v2 == best && i2 < bi)) {
+                        best = v2;
+                        bi = i2;
+                    }
+                }
+                if (lane < 16 && m < a.M) {
+                    a.arg_val[(size_t)m * n_parts + gb0 / 4] = best;
+                    a.arg_idx[(size_t)m * n_parts + gb0 / 4] = bi;
+                }
+            }
+        }
     } else {  // EPI_RESID
         if (gb0 < a.NB) {
             const int nsq = a.d / 64;
@@ -807,6 +859,11 @@ hipError_t launch_pf_gemm(const PfArgs &a, const PfPlan &p, int epi, hipStream_t
         return pf_launch_epi<EPI_QKV>(a, p.shape, p.tt, s);
     }
     if (epi == EPI_SWIGLU) return pf_launch_epi<EPI_SWIGLU>(a, p.shape, p.tt, s);
+    if (epi == EPI_LOGITS) {
+        if (p.shape != PF_STEP_PLAN.shape || p.tt != PF_STEP_PLAN.tt || a.scale || !a.arg_val || !a.arg_idx)
+            return hipErrorInvalidValue;
+        return pf_launch<EPI_LOGITS, PF_STEP_PLAN.shape, PF_STEP_PLAN.tt, false>(a, s);
+    }
     return hipErrorInvalidValue;
 }
 
