@@ -11,7 +11,9 @@
 //                      LOGITS -> 1/rms, logits + per-group argmax
 //   k_attn_mfma      tree-masked attention over the cache, split over keys
 //   k_accept         vocab-wide argmax reduce + greedy acceptance walk
-//   k_accept_sampled speculative sampling walk over full logits rows (T > 0)
+//   k_sample_nodes   the speculative sampling rule's decisions, a workgroup per
+//                    node (T > 0); the host walks them.  k_accept_sampled walks
+//                    in one workgroup, for the largest vocabularies
 //   k_kv_commit      in-place compaction of the accepted path
 //
 // Weights are bf16 or fp32, activations and accumulation fp32.  Every
