@@ -5,7 +5,7 @@
     python -m paper_2412_18934_amd.profiling mfma <counter_collection.csv> <out.txt> <command>
 
 ``stats`` writes a per-kernel table (calls, average, share) plus the average
-duration of the projection kernels (k_proj, k_gemm_valu), the figure bench.py's roofline
+duration of the projection kernels (k_proj, k_gemm_valu, k_pf_gemm), the figure bench.py's roofline
 uses.  ``hbm`` turns FETCH_SIZE / WRITE_SIZE (KiB per dispatch) into bytes per
 dispatch, scaled by what the same counters read for a plain copy of known
 size: the weight-packing kernel k_pack_blocks, which at init reads every
@@ -30,7 +30,7 @@ import sys
 PKG = os.path.dirname(os.path.abspath(__file__))
 KERNEL_SOURCES = ("csrc/dv_kernels.hip", "csrc/dv_prefill.hip", "csrc/dv_engine.cpp", "csrc/dv_device.h",
                   "csrc/dv_internal.h")
-PROJ_PREFIXES = ("k_proj", "k_gemm")
+PROJ_PREFIXES = ("k_proj", "k_gemm", "k_pf_gemm")
 REF_KERNEL = "k_pack_blocks"
 CLOCK_HZ = 2.4e9      # peak engine clock
 N_SIMD = 256 * 4      # compute units x SIMDs
@@ -67,7 +67,7 @@ def summarize_stats(stats_csv, trace_csv, out_path, command):
         if is_projection(name):
             gemm_ns += float(r["TotalDurationNs"])
             gemm_n += n
-    lines += ["", "Projection kernels (k_proj, k_gemm_valu): %d launches, average %.2f us."
+    lines += ["", "Projection kernels (k_proj, k_gemm_valu, k_pf_gemm): %d launches, average %.2f us."
               % (gemm_n, gemm_ns / max(gemm_n, 1) / 1e3)]
     # one full greedy step from the trace: the span between two k_accept
     # dispatches (the sampled leg that follows ends in k_accept_sampled)
