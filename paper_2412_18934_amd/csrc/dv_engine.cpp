@@ -646,9 +646,8 @@ int prefill_large(dv_handle *h, const int32_t *tokens, int n, dv_kv *kv, int32_t
         base.x = h->pf_x;
         base.us = h->pf_us;
         base.ssq_out = h->pf_ssq;
-        const PfPlan plan_qkv = pf_plan(3 * d / 16, MT, d, q8, q8 ? 2 : 1, h->n_cu),
-                     plan_o = pf_plan(d / 16, MT, d, q8, 1, h->n_cu), plan_gu = pf_plan(F / 8, MT, d, q8, 1, h->n_cu),
-                     plan_down = pf_plan(d / 16, MT, F, q8, 1, h->n_cu);
+        const PfPlan plan_qkv = pf_plan(3 * d / 16, MT, d, q8, h->n_cu), plan_o = pf_plan(d / 16, MT, d, q8, h->n_cu),
+                     plan_gu = pf_plan(F / 8, MT, d, q8, h->n_cu), plan_down = pf_plan(d / 16, MT, F, q8, h->n_cu);
         auto gemm = [&](const PfPlan &p, int epi, const uint16_t *packed, const float *scale, int rows, int K,
                         const uint16_t *xs, const void *gain) -> int {
             PfArgs a = base;

@@ -283,7 +283,7 @@ hipError_t launch_pf_embed(const int32_t *tokens, const void *embed, int M, int 
 struct PfPlan {
     int shape, tt, n_tt, ks;
 };
-PfPlan pf_plan(int NB, int MT, int K, bool q8, int min_parts, int n_cu);
+PfPlan pf_plan(int NB, int MT, int K, bool q8, int n_cu);
 // the prefill GEMM addresses a matrix with 31-bit byte offsets
 inline bool pf_addressable(int NB, int K, bool q8) { return (double)NB * K * (q8 ? 16 : 32) < 2147483648.0; }
 // Whether a bf16 projection of NB blocks without K splits, over a verify step's

@@ -70,6 +70,17 @@ __global__ __launch_bounds__(PF_THREADS) void k_pf_embed(const int32_t *tokens, 
 // before it counts itself), and the unit of a tile that counts last adds them
 // in range order and runs the epilogue, so every sum has a fixed order and no
 // workgroup waits for another.
+//
+// int8 QKV (STEP_SUM) adds up each 64-column step by itself, lo parts first,
+// and adds that to the running sums: an MFMA rounds at the size of what it
+// accumulates into, and in one chain those are 4 roundings per step at the size of
+// the whole sum instead of 1.  The keys and values are rounded to bf16 next,
+// so every error here moves some of them to the other side of a midpoint, and
+// all later layers attend to those.  Relative error of all K/V against 64 bits, two
+// 13B layers, 500 tokens: 2.9e-4, 3.7e-4 in one chain (3.4e-4 through the
+// verify kernels, whose sums are 4 shorter chains); of layer 0's 2.2e-5,
+// 3.7e-5 (3.1e-5).  The same for O, gate/up and down changes neither figure.
+// It costs 1% of that prefill (1206 -> 1217 us), at every projection 7%.
 template <int EPI, int NWR, int NKG, int TT, int LEAD, bool Q8>
 __global__ __launch_bounds__(64 * NWR * NKG) void k_pf_gemm(PfArgs a)
 {
@@ -81,6 +92,7 @@ __global__ __launch_bounds__(64 * NWR * NKG) void k_pf_gemm(PfArgs a)
     constexpr int TI = (TT + NKG - 1) / NKG;  // token tiles per K group after the sums
     // blocks of the K groups' sums exchanged at a time, as LDS allows
     constexpr int HB = TT * (NKG - 1) * NWR * BW <= 150 ? BW : 2;
+    constexpr bool STEP_SUM = Q8 && EPI == EPI_QKV;
     constexpr int XN = NKG * 2 * XE, RN = TT * (NKG - 1) * NWR * HB * 64;
     __shared__ u32x4 xsm[XN > RN ? XN : RN];
     __shared__ float rinv_s[16 * TT];
@@ -154,6 +166,7 @@ __global__ __launch_bounds__(64 * NWR * NKG) void k_pf_gemm(PfArgs a)
             lv[q & 1] = x[(hf * TT + t) * 128 + 64];
         };
         bread(0);
+        f32x4 sum[BW];  // STEP_SUM: of this step and tile
 #pragma unroll
         for (int q = 0; q < SK * TT; ++q) {
             const int t = q / SK, hf = q % SK;
@@ -171,10 +184,31 @@ __global__ __launch_bounds__(64 * NWR * NKG) void k_pf_gemm(PfArgs a)
                     w[b] = __builtin_bit_cast(bf16x8, wb[j][b]);
                 }
             }
+            if constexpr (STEP_SUM) {
 #pragma unroll
-            for (int b = 0; b < BW; ++b) acc[t][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[b], hi, acc[t][b], 0, 0, 0);
+                for (int b = 0; b < BW; ++b) {
+                    if (hf == 0) sum[b] = (f32x4){0.f, 0.f, 0.f, 0.f};
+                    sum[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[b], lo, sum[b], 0, 0, 0);
+                }
 #pragma unroll
-            for (int b = 0; b < BW; ++b) acc[t][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[b], lo, acc[t][b], 0, 0, 0);
+                for (int b = 0; b < BW; ++b) sum[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[b], hi, sum[b], 0, 0, 0);
+                if (hf == SK - 1) {
+                    // (the empty asm keeps each addition in its place: left to
+                    // the end of the step they hold every tile's sums at once)
+#pragma unroll
+                    for (int b = 0; b < BW; ++b) {
+                        acc[t][b] += sum[b];
+                        asm volatile("" : "+v"(acc[t][b]));
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int b = 0; b < BW; ++b)
+                    acc[t][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[b], hi, acc[t][b], 0, 0, 0);
+#pragma unroll
+                for (int b = 0; b < BW; ++b)
+                    acc[t][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[b], lo, acc[t][b], 0, 0, 0);
+            }
             __builtin_amdgcn_sched_barrier(0);
         }
     };
@@ -736,7 +770,8 @@ hipError_t launch_pf_embed(const int32_t *tokens, const void *embed, int M, int 
 namespace {
 
 // Workgroup shapes: rows per unit and K groups; a shape's steps in flight are
-// what its registers hold (8 waves of 256 VGPRs, no spills).
+// what its registers hold (8 waves of 256 VGPRs; only int8 QKV at 128 rows and 8
+// tiles spills, two address registers reloaded per step).
 constexpr int SHAPE_NWR[3] = {8, 4, 2};
 constexpr int PF_TT_MIN = 4, PF_TT_MAX = 8, PF_KS_MAX = 8;
 
@@ -799,13 +834,7 @@ hipError_t pf_launch_epi(const PfArgs &a, int shape, int tt, hipStream_t s)
 // O 84 -> 30, gate/up 170 -> 75, down 206 -> 49 (38 and 57 for O and down while
 // one K group's waves did all sums, folds and epilogues); 1024 tokens, 13B width,
 // inside the model: 248 -> 245, 125 -> 116, 473 -> 454, 302 -> 255.
-//
-// min_parts: the least number of parts (K groups x ranges) a sum is added from.
-// A single chain of MFMAs over K = 5120 rounds 320 times at the sum's size;
-// for int8 QKV, where 64-token passes of the verify kernels sum in 4 parts,
-// that put 0.040% of layer 0's keys on the other side of a bf16 midpoint
-// against 0.030%, and every later layer inherits those, so it takes 2 parts.
-PfPlan pf_plan(int NB, int MT, int K, bool q8, int min_parts, int n_cu)
+PfPlan pf_plan(int NB, int MT, int K, bool q8, int n_cu)
 {
     struct Fit {
         double a, b, c;
@@ -828,7 +857,6 @@ PfPlan pf_plan(int NB, int MT, int K, bool q8, int min_parts, int n_cu)
         for (int n_tt = n_min; n_tt <= std::max(MT / PF_TT_MIN, n_min); ++n_tt) {
             const int tt = std::max((MT + n_tt - 1) / n_tt, PF_TT_MIN);
             for (int ks = 1; ks <= PF_KS_MAX && ks * nkg <= S; ++ks) {
-                if (ks * nkg < min_parts) continue;
                 const long units = (long)n_rt * n_tt * ks;
                 if (ks > 1 && units * nwr * 4 * tt > DV_PF_PART_TILES) break;
                 const long rounds = (units + n_cu - 1) / n_cu;
