@@ -1,4 +1,8 @@
-"""The prefill GEMM's sums against 64 bits.
+"""Every instantiation of the prefill GEMM (epilogue, workgroup shape, token
+tiles per unit, one K range and several, bf16 and int8 weights) against
+64 bits, on small matrices with ragged rows, tokens and steps: row tiles that
+end early, a token group one tile short, padding tokens, K groups and ranges
+that share the steps unevenly.
 
 Operands are exact in the kernel's formats (the reference takes hi + lo of the
 split activations), so an output is off by the sums' rounding and, where it is
@@ -163,6 +167,32 @@ def _plan(shape, tt, n_tt, ks):
 
 
 @pytest.mark.parametrize("q8", [False, True], ids=["bf16", "i8"])
+@pytest.mark.parametrize("epi", [P.EPI_QKV, P.EPI_RESID, P.EPI_SWIGLU], ids=["qkv", "resid", "swiglu"])
+@pytest.mark.parametrize("shape", [0, 1, 2])
+def test_every_instantiation(epi, q8, shape):
+    if q8 and shape == 2:
+        pytest.skip("not built")
+    for tt in (4, 5, 6, 7, 8):
+        for n_tt, ks in ((1, 1), (3, 1), (2, 3), (1, 2)):
+            # the last group of several is one tile short (4 tiles are never less)
+            mt = n_tt * tt - (1 if n_tt > 1 and tt > 4 else 0)
+            if n_tt == 1 and ks == 1 and tt == 4:
+                mt = 3                          # the smallest chunk: 3 tiles in a group of 4
+            d, hd = (320, 64) if tt % 2 else (384, 128)
+            k = {P.EPI_RESID: 1216 if q8 else 1120, P.EPI_QKV: d, P.EPI_SWIGLU: d}[epi]
+            if epi != P.EPI_RESID and ks * (8 // P.SHAPE_NWR[shape]) > k // (64 if q8 else 32):
+                ks = 1
+            nb = {P.EPI_QKV: 3 * d // 16, P.EPI_RESID: d // 16, P.EPI_SWIGLU: 44}[epi]
+            pr = Problem(epi, q8, nb, k, d, hd, mt, 16 * mt - 5, 1000 + 100 * shape + 10 * tt + n_tt)
+            p = _plan(shape, tt, n_tt, ks)
+            print("[pf] %s %s shape %d tt %d n_tt %d ks %d" % (NAMES[epi], "i8" if q8 else "bf16", shape, tt, n_tt, ks),
+                  end="", flush=True)
+            P.launch(pr.args(p), p, epi)
+            torch.cuda.synchronize()
+            print("  " + " ".join("%.2e" % e for e in pr.check(p)), "bar %.2e" % pr.bar(p), flush=True)
+
+
+@pytest.mark.parametrize("q8", [False, True], ids=["bf16", "i8"])
 @pytest.mark.parametrize("shape,tt,ks", [(0, 8, 1), (0, 8, 4), (1, 8, 1), (1, 7, 2), (2, 6, 1)])
 def test_sums_over_a_whole_model_width(q8, shape, tt, ks):
     """K = 5120 (160 k-steps): the rounding of long chains, on the queries,
@@ -175,3 +205,17 @@ def test_sums_over_a_whole_model_width(q8, shape, tt, ks):
     torch.cuda.synchronize()
     print("[pf] K = 5120 %s shape %d tt %d ks %d: " % ("i8" if q8 else "bf16", shape, tt, ks), pr.check(p),
           "bar %.2e" % pr.bar(p), flush=True)
+
+
+@pytest.mark.parametrize("mt,m", [(3, 33), (3, 48), (4, 49), (4, 64)])
+@pytest.mark.parametrize("out", ["aligned", "unaligned", "none"])
+def test_logits(mt, m, out):
+    """The wide trees' lm_head: vector and scalar stores, and no logits at all."""
+    pr = Problem(P.EPI_LOGITS, False, 36, 320, 320, 64, mt, m, 3000 + m)
+    p = _plan(2, 4, 1, 1)
+    a = pr.args(p)
+    a.logits = {"aligned": pr.buf["logits"].data_ptr(), "unaligned": pr.buf["logits"].data_ptr() + 4, "none": None}[out]
+    pr.buf["logits_at"] = a.logits
+    P.launch(a, p, P.EPI_LOGITS)
+    torch.cuda.synchronize()
+    pr.check(p)

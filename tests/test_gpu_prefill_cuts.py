@@ -1,9 +1,10 @@
-"""Prefill at the sizes where the prefill GEMM is cut differently: one token
-group and several (even and uneven), one K range and several, row tiles that
-end early, the smallest chunk (a prompt just above a small max_tree, and the
-one-token rest of a 1025-token prompt), bf16 and int8 weights, on an empty and
-on a cached prefix.  Bars as in test_gpu_prefill.py, whose oracle comparison
-this reuses."""
+"""Whole prefills at the lengths where the cut of the prefill GEMM changes: one
+token group and several (even and uneven), one K range and several, row tiles
+that end early, the smallest chunk (a prompt just above a small max_tree, and
+the one-token rest of a 1025-token prompt), bf16 and int8 weights, on an empty
+and on a cached prefix.  These small widths take few of the GEMM's
+instantiations (128- and 256-row workgroups mostly); test_gpu_pf_gemm.py runs each.
+Bars as in test_gpu_prefill.py, whose oracle comparison this reuses."""
 import numpy as np
 import pytest
 
