@@ -588,9 +588,12 @@ int pf_reserve(dv_handle *h, int tokens, bool split)
     char *b = nullptr;
     if (hipMalloc((void **)&b, total) != hipSuccess)
         return set_err(h, DV_ENOMEM, "prefill workspace for %d tokens: allocation failed", tokens);
-    if (split && hipMemset(b + o_cnt, 0, cnt_bytes) != hipSuccess) {
+    // (on the handle's stream: the GEMMs that count follow there, and a
+    // non-blocking stream does not wait for the null stream)
+    const hipError_t e = split ? hipMemsetAsync(b + o_cnt, 0, cnt_bytes, h->stream) : hipSuccess;
+    if (e != hipSuccess) {
         (void)hipFree(b);
-        return set_err(h, DV_ENOMEM, "prefill workspace for %d tokens: clearing failed", tokens);
+        return hip_fail(h, e, "prefill workspace clear");
     }
     h->pf_block = b;
     h->pf_tok = (int32_t *)(b + o_tok);

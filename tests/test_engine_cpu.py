@@ -1,0 +1,84 @@
+"""The host engine (dv_engine.cpp) compiled for the CPU against a logging
+stand-in for the HIP runtime and the kernel launchers (hipstub.cpp): the order of
+clears, launches and waits, and what happens when memory runs out."""
+import ctypes
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+from paper_2412_18934_amd import dv
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+CSRC = os.path.join(ROOT, "paper_2412_18934_amd", "csrc")
+STREAM = 0x1230
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("engine") / "libengine.so")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-Wl,-Bsymbolic", "-D__HIP_PLATFORM_AMD__",
+                    "-I", "/opt/rocm/include", "-I", os.path.join(ROOT, "include"), "-I", CSRC,
+                    os.path.join(CSRC, "dv_engine.cpp"), os.path.join(HERE, "hipstub.cpp"), "-o", out], check=True)
+    L = ctypes.CDLL(out)
+    L.stub_log.restype = ctypes.c_char_p
+    L.stub_reset.argtypes = [ctypes.c_size_t]
+    L.stub_live.restype = ctypes.c_size_t
+    L.dv_last_error.restype = ctypes.c_char_p
+    L.dv_last_error.argtypes = [ctypes.c_void_p]
+    return L
+
+
+class Engine:
+    def __init__(self, lib, dtype, n_layers=2, d=256, ffn=704, vocab=1024, max_ctx=4096, max_tree=8, stream=STREAM):
+        self.lib = lib
+        cfg = dv.dv_config(n_layers=n_layers, d_model=d, n_heads=d // 64, head_dim=64, d_ffn=ffn, vocab=vocab,
+                           rms_eps=1e-6, rope_base=10000.0, weight_dtype=dtype, max_ctx=max_ctx, max_tree=max_tree)
+        tab = ctypes.cast((ctypes.c_void_p * n_layers)(*([0x1000] * n_layers)), ctypes.POINTER(ctypes.c_void_p))
+        w = dv.dv_weights(0x1000, 0x1000, 0x1000, *[tab] * 9, 0x1000, *[tab] * 7)
+        self.h = ctypes.c_void_p()
+        lib.stub_reset(2 ** 64 - 1)
+        assert lib.dv_verify_init(ctypes.byref(cfg), ctypes.byref(w), ctypes.c_void_p(stream), ctypes.byref(self.h)) == 0
+        self.init_log = self.log()
+        self.kv = dv.dv_kv(0x1000, 0x1000, max_ctx, 0)
+
+    def log(self):
+        rows = [r.split() for r in self.lib.stub_log().decode().splitlines()]
+        return [(what, int(stream, 16), int(n)) for what, stream, n in rows]
+
+    def prefill(self, n, fail_at=2 ** 64 - 1):
+        self.lib.stub_reset(fail_at)
+        toks = np.zeros(n, np.int32)
+        nxt = ctypes.c_int32()
+        return self.lib.dv_prefill(self.h, toks.ctypes.data_as(ctypes.c_void_p), n, ctypes.byref(self.kv),
+                                   ctypes.byref(nxt))
+
+    def close(self):
+        self.lib.dv_verify_free(self.h)
+
+
+@pytest.fixture(params=[dv.DV_BF16, dv.DV_I8], ids=["bf16", "i8"])
+def engine(request, lib):
+    e = Engine(lib, request.param)
+    yield e
+    e.close()
+    assert lib.stub_live() == 0
+
+
+def test_clears_are_ordered_before_the_launches(engine):
+    """A memset on the null stream is not ordered before launches on a
+    non-blocking stream: either it goes on the handle's stream, or the device is
+    synchronised in between."""
+    assert engine.prefill(300) == 0
+    pending = False
+    for what, stream, _ in engine.log():
+        if what == "memset" and stream != STREAM:
+            pending = True
+        elif what == "devsync":
+            pending = False
+        elif what in ("pf_embed", "pf_gemm", "causal", "gemm", "norm", "attention", "accept"):
+            assert stream == STREAM
+            assert not pending, what
+    assert [w for w, _, _ in engine.log()].count("pf_gemm") == 4 * 2

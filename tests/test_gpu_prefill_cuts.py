@@ -76,3 +76,24 @@ def test_prefill_attention_key_groups(heads, n, p0):
         _check(case, n, p0, 5500 + n)
     finally:
         case.close()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "i8"])
+def test_first_prefill_on_a_side_stream(dtype):
+    """A handle bound to a non-blocking stream, whose first prefill cuts K: the
+    same bytes as on the default stream."""
+    case = _case(dtype, 1024, 8, 2816, 160)
+    side = torch.cuda.Stream()
+    h2 = dv.dv_verify_init(case.ccfg, case.dev.c, side.cuda_stream)
+    try:
+        prompt = synth.prompt(5700, 130, case.cfg.vocab)
+        kv = [case.new_kv(fill=float("nan")) for _ in range(2)]
+        torch.cuda.synchronize()
+        nxt = dv.dv_prefill(h2, prompt, kv[0].c)
+        assert dv.dv_prefill(case.h, prompt, kv[1].c) == nxt
+        for l in range(case.cfg.n_layers):
+            a, b = (x.layer_host(l, 130) for x in kv)
+            assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
+    finally:
+        dv.dv_verify_free(h2)
+        case.close()
