@@ -84,8 +84,11 @@ typedef struct dv_config {
 /* Device pointers to weights, all of weight_dtype (for DV_I8: projection
  * matrices int8, embed and norm gains bf16, plus the per-row scales).  The
  * per-layer fields are HOST arrays of n_layers device pointers; they are
- * copied at init, the weights themselves are not copied and must outlive the
- * handle.  The *_scale fields are read only for DV_I8 (NULL otherwise). */
+ * copied at init.  The weights must outlive the handle.  DV_F32: all of them
+ * are read in place by every call.  DV_BF16 and DV_I8: the projection
+ * matrices (and row scales) are copied into the kernels' order at init, so later
+ * writes to the caller's are not seen; embed and the norm gains (and w_down
+ * where d_ffn is not a multiple of 32) are read in place.  The *_scale fields are read only for DV_I8 (NULL otherwise). */
 typedef struct dv_weights {
     const void *embed;       /* [vocab][d_model]                 */
     const void *final_norm;  /* [d_model]                        */

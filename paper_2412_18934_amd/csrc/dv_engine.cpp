@@ -1014,27 +1014,18 @@ int dv_verify_init(const dv_config *cfg, const dv_weights *w, void *stream, dv_h
             return set_err(nullptr, DV_EHIP, "rope table upload failed");
         }
     }
-    // keep the projection matrices in block order (one extra copy of the
-    // projection weights in HBM, written once here).  The fp32 kernel can
-    // also read the caller's rows (at half the rate): the copy of fp32 weights
-    // is made only while it takes at most half of the free memory, so that
-    // models which filled the card without it still do.
-    bool packed = mf;
-    if (h->wkind == W_F32) {
-        const double need = 4.0 * ((double)c.n_layers * (4.0 * d * d + 3.0 * d * F) + (double)V * d);
-        size_t free_b = 0, total_b = 0;
-        packed = hipMemGetInfo(&free_b, &total_b) == hipSuccess && need <= 0.5 * (double)free_b;
-    }
-    if (packed) {
+    // MFMA path: keep the projection matrices in block order (one extra copy of
+    // the projection weights in HBM, written once here).  fp32 weights are read in
+    // place.
+    if (mf) {
         // int8: the weights keep one byte each and the row scales follow the
         // packed row order
         auto pack = [&](const GemmPlan &p, int epi, const void *w0, const void *w1, const void *w2,
                         const float *s0, const float *s1, const float *s2, int N, int K, uint16_t **dst,
                         float **sdst) -> bool {
-            if (!p.rb) return true;  // the VALU kernel reads the caller's rows
+            if (!p.mfma) return true;  // the VALU kernel reads the caller's rows
             const size_t elems = (size_t)p.n_tiles * DV_GEMM_TILE * K;
-            const size_t wsz = h->wkind == W_I8 ? 1 : (h->wkind == W_BF16 ? 2 : 4);
-            if (hipMalloc((void **)dst, elems * wsz) != hipSuccess) return false;
+            if (hipMalloc((void **)dst, elems * (h->wkind == W_I8 ? 1 : 2)) != hipSuccess) return false;
             GemmArgs a{};
             a.w0 = w0;
             a.w1 = w1;

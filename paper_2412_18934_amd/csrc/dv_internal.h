@@ -78,14 +78,12 @@ enum GemmEpi { EPI_QKV = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_LOGITS = 3, EPI_P
 // l%16, columns 64 p + 8 (l/16) .. +8 in bytes 0-7 and 64 p + 32 + 8 (l/16)
 // .. +8 in bytes 8-15 -- starts at byte ((p G + g) rb + b) 1024; the row
 // scales follow the packed row order (block gb = g rb + b, row r at gb 16 + r).
-// fp32 weights use 16-column steps: the 1 KB block of (step s, block gb) --
-// 16 rows x 16 columns, lane l holding row l%16, columns 16 s + 4 (l/16) .. +4
-// -- starts at float (s 2 n_tiles + gb) 256.
+// fp32 weights are read in place, in the caller's rows.
 enum WeightKind { W_F32 = 0, W_BF16 = 1, W_I8 = 2 };
 
 struct GemmArgs {
     const void *w0, *w1, *w2;  // QKV: wq, wk, wv; SWIGLU: w_gate, w_up; else w0
-    const uint16_t *packed;    // the weights in block order (above); null: rows (VALU kernel, fp32 without a copy)
+    const uint16_t *packed;    // the weights in block order (above); null: rows (VALU kernel, fp32)
     const float *s0, *s1, *s2; // int8: per-row scales of w0, w1, w2 (packing only)
     const float *scale;        // int8: the row scales in packed row order
     int32_t N;                 // rows of one matrix (d_model, d_ffn or vocab)

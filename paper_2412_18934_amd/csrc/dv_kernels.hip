@@ -141,9 +141,9 @@ __device__ __forceinline__ void rinv_finish(const GemmArgs &a, const float (&v)[
 // thread's first NJ partials before the weight stream starts (a wave's loads
 // return in order, so they are back before the first weights and waiting for
 // them empties nothing), finish consumes them once the first weight steps
-// have been requested.  7B, 16 nodes: QKV 48 -> 38 us, gate/up 79 -> 71,
-// lm_head 88 -> 78 against input_rinv with clamped loads; the bf16 and int8
-// kernels gain under 1% and keep the order above.
+// have been requested.  7B, 16 nodes, with weights packed in lane order: QKV 48 ->
+// 38 us, gate/up 79 -> 71, lm_head 88 -> 78 against input_rinv with clamped loads;
+// the bf16 and int8 kernels gain under 1% and keep the order above.
 template <int NT, int MT> struct Rinv {
     static constexpr int TPT = NT / (MT == 1 ? 16 : (MT == 2 ? 32 : 64));
     static constexpr int NJ = TPT >= 16 ? 8 : (TPT >= 8 ? 12 : 24);
@@ -554,20 +554,6 @@ __global__ __launch_bounds__(64) void k_pack_blocks_i8(GemmArgs a, int epi, uint
     }
 }
 
-// fp32 weights: the 1 KB block of (16-column step s, block gb) takes 16 bytes
-// of row l % 16 per lane.
-__global__ __launch_bounds__(64) void k_pack_blocks_f32(GemmArgs a, int epi, float *dst)
-{
-    const int gb = blockIdx.x, lane = threadIdx.x;
-    const RowMap rm = row_map(a, epi, gb >> 1);
-    const int h = gb & 1;
-    const float *src = reinterpret_cast<const float *>(rm.ptr[h]) + (size_t)(rm.row0[h] + (lane & 15)) * a.K +
-                       (lane >> 4) * 4;
-    for (int s = blockIdx.y; s < a.K / 16; s += gridDim.y)
-        *reinterpret_cast<float4 *>(dst + ((size_t)s * gridDim.x + gb) * 256 + lane * 4) =
-            *reinterpret_cast<const float4 *>(src + 16 * s);
-}
-
 // Row scales in packed row order: block gb, row r -> dst[16 gb + r].
 __global__ __launch_bounds__(16) void k_pack_scales(GemmArgs a, int epi, float *dst)
 {
@@ -812,18 +798,21 @@ __global__ __launch_bounds__(64 * NW) void k_proj(GemmArgs a)
 // rate (256 flop per CU and clock) at 64.
 //
 // A step is 16 columns: lane l holds the 4 consecutive columns 4 (l / 16) ..
-// of weight row l % 16 (one 16-byte load per 16-row block) and the same
+// of weight row l % 16 (16 bytes per 16-row block) and the same
 // columns of token l % 16, and MFMA i takes component i of both, i.e. columns
-// 4 g + i, g = 0..3.  The weights come from the packed copy (k-major: the 1 KB
-// block of (step s, block b of NB) at float (s NB + b) 256, lane order) or,
-// where none is kept, from the caller's rows (64 bytes per row and load, a
-// wave taking steps in pairs so that it uses whole 128-byte lines).  Same
-// kernel, other strides; measured on 22016 x 4096 and 12288 x 4096, 16
-// tokens: 5.4 and 6.3 TB/s packed, 3.2 and 3.3 from rows.  Units, K splits,
-// the wave partials' sum in LDS and the epilogues are k_proj's.
+// 4 g + i, g = 0..3.  The weights are the caller's rows, read in place: loaded in
+// that order, a quarter wave's 16 lanes touch 16 rows and so 16 cache lines
+// (two 7B layers and the head, 16
+// nodes: 837 us, 515 with the turn).  A wave therefore takes steps in pairs and
+// loads a block's pair as 2 x 8 rows of 128 contiguous bytes, 8 lanes a row, and turns
+// it through LDS that only this wave uses (16-byte chunk c of row r at c ^ (r % 8),
+// so neither side has bank conflicts).  Units, K splits, the wave partials' sum
+// in LDS and the epilogues are k_proj's.
 // 7B width, 16 tokens, against the VALU kernel it replaces (8 lanes per row,
-// every row's lanes loading the activations again): QKV 174 -> 38 us, O 106 ->
-// 18, gate/up 243 -> 71, down 275 -> 34, lm_head 318 -> 78.
+// every row's lanes loading the activations again): QKV 174 -> 43 us, O and
+// down together 381 -> 66, gate/up 243 -> 86, lm_head 318 -> 102 (4.7, 3.7, 4.2 and
+// 5.2 TB/s; a packed copy of the weights in lane order reaches 5.4 to 6.3, but
+// doubles their memory and does not follow the caller's writes).
 template <int MT, int EPI, int NW, int U, int RB>
 __global__ __launch_bounds__(64 * NW) void k_proj_f32(GemmArgs a)
 {
@@ -834,7 +823,8 @@ __global__ __launch_bounds__(64 * NW) void k_proj_f32(GemmArgs a)
     constexpr int SXN = (16 * MT * ROWS + 64 * NW - 1) / (64 * NW);  // RESID: x values per thread
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n16 = lane & 15, g4 = lane >> 4;
     const int K = a.K, S = K / 16, KS = a.ks;
-    __shared__ f32x4 red[NW][NE / 64][64];
+    // a wave's turned weights (2 KB per block), later its partial sums
+    __shared__ f32x4 red[NW][NE / 64 > 2 * RB ? NE / 64 : 2 * RB][64];
     __shared__ float Y[16 * MT * LD];
     __shared__ float rinv[DV_TREE_MAX];
     __shared__ int last_s;
@@ -844,25 +834,15 @@ __global__ __launch_bounds__(64 * NW) void k_proj_f32(GemmArgs a)
     for (int unit = blockIdx.x; unit < a.n_units; unit += gridDim.x) {
         const int g = unit / KS, ks = unit - g * KS;
         const int sb = (ks * S) / KS, T = ((ks + 1) * S) / KS - sb;  // this unit's steps
-        // pairs of steps go round the waves: wave w has steps 2 w, 2 w + 1,
-        // 2 (w + NW), ...
-        const int rem = T % (2 * NW) - 2 * wave;
-        const int n = 2 * (T / (2 * NW)) + (rem < 0 ? 0 : (rem > 2 ? 2 : rem));
-        auto step = [&](int i) { return sb + 2 * NW * (i >> 1) + 2 * wave + (i & 1); };
-        const float *wp[RB];
+        // pairs of steps go round the waves: wave w has the pairs w, w + NW, ...
+        // (the unit's last pair may be a single step)
+        const int np = (T + 1) / 2, n = wave < np ? (np - wave + NW - 1) / NW : 0;
         const int xlane = n16 * K + 4 * g4;
-        int wlane = 4 * lane;
-        size_t wstep = (size_t)a.n_tiles * 512;
+        const float *wp[RB];
 #pragma unroll
-        for (int b = 0; b < RB; ++b) wp[b] = reinterpret_cast<const float *>(a.packed) + (size_t)(g * RB + b) * 256;
-        if (!a.packed) {
-            wlane = xlane;
-            wstep = 16;
-#pragma unroll
-            for (int b = 0; b < RB; ++b) {
-                const RowMap rm = row_map(a, EPI, (g * RB + b) >> 1);
-                wp[b] = reinterpret_cast<const float *>(rm.ptr[b & 1]) + (size_t)rm.row0[b & 1] * K;
-            }
+        for (int b = 0; b < RB; ++b) {
+            const RowMap rm = row_map(a, EPI, (g * RB + b) >> 1);
+            wp[b] = reinterpret_cast<const float *>(rm.ptr[b & 1]) + (size_t)(rm.row0[b & 1] + (lane >> 3)) * K;
         }
         f32x4 acc[RB][MT];
 #pragma unroll
@@ -884,30 +864,58 @@ __global__ __launch_bounds__(64 * NW) void k_proj_f32(GemmArgs a)
             if (!have_rinv) RV::load(a, sv);
         }
         if (n > 0) {
-            f32x4 wb[U][RB], xb[U][MT];
-            auto fetch = [&](int j, int i) {
-                const int st = step(i);
+            f32x4 wb[U][RB][2], xb[U][2][MT];
+            auto fetch_w = [&](int j, int i) {
+                // (a single last step's other half may lie past the row)
+                int c = 16 * (sb + 2 * (wave + NW * i)) + 4 * (lane & 7);
+                c = c < K ? c : c - 16;
 #pragma unroll
                 for (int b = 0; b < RB; ++b)
-                    wb[j][b] = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(wp[b] + st * wstep + wlane));
 #pragma unroll
-                for (int mt = 0; mt < MT; ++mt)
-                    xb[j][mt] = *reinterpret_cast<const f32x4 *>(a.x + (size_t)(16 * mt) * K + 16 * st + xlane);
+                    for (int h = 0; h < 2; ++h)
+                        wb[j][b][h] =
+                            __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(wp[b] + (size_t)(8 * h) * K + c));
             };
-            auto mfma = [&](int j) {
+            auto fetch_x = [&](int j, int i) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const int st = min(sb + 2 * (wave + NW * i) + h, S - 1);
+#pragma unroll
+                    for (int mt = 0; mt < MT; ++mt)
+                        xb[j][h][mt] = *reinterpret_cast<const f32x4 *>(a.x + (size_t)(16 * mt) * K + 16 * st + xlane);
+                }
+            };
+            // the pair of slot j through LDS (a wave's LDS operations complete in order)
+            f32x4 *const turn = &red[wave][0][0];
+            const int wr = 8 * (lane >> 3) + ((lane & 7) ^ (lane >> 3)), rd = 8 * n16, sw = n16 & 7;
+            auto stage = [&](int j) {
+#pragma unroll
+                for (int b = 0; b < RB; ++b)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) turn[b * 128 + 64 * h + wr] = wb[j][b][h];
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            };
+            auto mfma = [&](int j, int h) {
+                f32x4 w[RB];
+#pragma unroll
+                for (int b = 0; b < RB; ++b) w[b] = turn[b * 128 + rd + ((4 * h + g4) ^ sw)];
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
 #pragma unroll
                     for (int b = 0; b < RB; ++b)
 #pragma unroll
                         for (int mt = 0; mt < MT; ++mt)
-                            acc[b][mt] =
-                                __builtin_amdgcn_mfma_f32_16x16x4f32(wb[j][b][i], xb[j][mt][i], acc[b][mt], 0, 0, 0);
+                            acc[b][mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[b][i], xb[j][h][mt][i], acc[b][mt], 0, 0, 0);
             };
-            // U steps in flight (indices past the end re-read the last step
+            // U pairs in flight (indices past the end re-read the last pair
             // and are dropped)
 #pragma unroll
-            for (int j = 0; j < U; ++j) fetch(j, min(j, n - 1));
+            for (int j = 0; j < U; ++j) {
+                fetch_w(j, min(j, n - 1));
+                fetch_x(j, min(j, n - 1));
+            }
             __builtin_amdgcn_sched_barrier(0);
             if constexpr (NEED_RINV) {
                 if (!have_rinv) RV::finish(a, sv, rinv);
@@ -917,15 +925,22 @@ __global__ __launch_bounds__(64 * NW) void k_proj_f32(GemmArgs a)
             for (; i + U < n; i += U) {
 #pragma unroll
                 for (int j = 0; j < U; ++j) {
-                    mfma(j);
-                    fetch(j, min(i + j + U, n - 1));
-                    // keep step j's loads ahead of step j + 1's MFMAs
+                    stage(j);
+                    fetch_w(j, min(i + j + U, n - 1));
+                    mfma(j, 0);
+                    mfma(j, 1);
+                    fetch_x(j, min(i + j + U, n - 1));
+                    // keep pair j's loads ahead of pair j + 1's MFMAs
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
 #pragma unroll
-            for (int j = 0; j < U; ++j)
-                if (i + j < n) mfma(j);
+            for (int j = 0; j < U; ++j) {
+                if (i + j >= n) break;
+                stage(j);
+                mfma(j, 0);
+                if (2 * (wave + NW * (i + j)) + 1 < T) mfma(j, 1);
+            }
         }
         if constexpr (EPI == EPI_RESID) {
 #pragma unroll
@@ -2188,10 +2203,10 @@ static const void *proj_f32_mt(int mt)
 {
     switch (mt) {
     case 0:
-    case 1: return (const void *)k_proj_f32<1, EPI, 4, 4, RB>;
-    case 2: return (const void *)k_proj_f32<2, EPI, 4, 4, RB>;
-    case 3: return (const void *)k_proj_f32<3, EPI, 4, 4, RB>;
-    case 4: return (const void *)k_proj_f32<4, EPI, 4, 4, RB>;
+    case 1: return (const void *)k_proj_f32<1, EPI, 4, 2, RB>;
+    case 2: return (const void *)k_proj_f32<2, EPI, 4, 2, RB>;
+    case 3: return (const void *)k_proj_f32<3, EPI, 4, 2, RB>;
+    case 4: return (const void *)k_proj_f32<4, EPI, 4, 2, RB>;
     default: return nullptr;
     }
 }
@@ -2288,9 +2303,6 @@ hipError_t launch_pack(const GemmArgs &a, int epi, int wkind, void *dst, hipStre
     } else if (wkind == W_BF16) {
         hipLaunchKernelGGL(k_pack_blocks, dim3(a.n_groups * a.rb, std::min(a.K / 32, 64)), dim3(64), 0, s, a, epi,
                            static_cast<uint16_t *>(dst));
-    } else if (wkind == W_F32) {
-        hipLaunchKernelGGL(k_pack_blocks_f32, dim3(a.n_groups * a.rb, std::min(a.K / 16, 64)), dim3(64), 0, s, a, epi,
-                           static_cast<float *>(dst));
     } else {
         return hipErrorInvalidValue;
     }

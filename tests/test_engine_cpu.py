@@ -82,3 +82,13 @@ def test_clears_are_ordered_before_the_launches(engine):
             assert stream == STREAM
             assert not pending, what
     assert [w for w, _, _ in engine.log()].count("pf_gemm") == 4 * 2
+
+
+def test_fp32_weights_are_not_copied(lib):
+    d, ffn, vocab, layers = 1024, 2816, 8192, 4
+    e = Engine(lib, dv.DV_F32, n_layers=layers, d=d, ffn=ffn, vocab=vocab, max_ctx=64)
+    try:
+        assert not [r for r in e.init_log if r[0] == "pack"]
+        assert lib.stub_live() < 4 * layers * (4 * d * d + 3 * d * ffn) / 4
+    finally:
+        e.close()

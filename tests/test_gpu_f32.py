@@ -1,13 +1,14 @@
 """fp32 weights against the oracle at the sizes where the fp32 projection and
 attention kernels change: 2- and 4-block row groups, K splits and their
 remainders (d_ffn a multiple of 16 only), one to four token tiles, key splits
-of one tile per wave and longer ones, and weights read from the caller's rows
-when no packed copy is kept."""
+of one tile per wave and longer ones, and weights that change under the
+handle."""
 import numpy as np
 import pytest
 
 import synth
 from oracle import verify as ov
+from paper_2412_18934_amd import dv
 from tests.helpers import GpuCase, compare_step, small_cfg
 
 pytestmark = pytest.mark.gpu
@@ -49,32 +50,43 @@ def test_f32_step(d, heads, ffn, p, m):
         case.close()
 
 
-def test_f32_without_packed_copy():
-    """With less than twice the copy's bytes free, the kernels read the
-    caller's rows; the sums are the same, so the results are too."""
-    cfg = small_cfg(n_layers=1, d_model=1024, n_heads=8, head_dim=128, d_ffn=2816, vocab=32000,
-                    init_std=0.045)
-    packed = GpuCase(cfg, seed=7300, capacity=128)
-    rows = fill = None
+def test_f32_weights_are_read_in_place():
+    """A caller may write new values into its fp32 matrices: the next step uses
+    them, as a handle made from them does."""
+    cfg = small_cfg(n_layers=2, d_model=256, n_heads=4, head_dim=64, d_ffn=688, vocab=1024, init_std=0.09)
+    case = GpuCase(cfg, seed=7300, capacity=128)
+    fresh = None
     try:
-        torch.cuda.empty_cache()
-        copy = 4 * (4 * 1024 * 1024 + 3 * 1024 * 2816 + 32000 * 1024)
-        weights = packed.dev.nbytes()
-        room = int(1.6 * copy) + weights
-        fill = torch.empty(max(torch.cuda.mem_get_info()[0] - room, 0), dtype=torch.uint8, device="cuda:0")
-        rows = GpuCase(cfg, seed=7300, capacity=128, weights=packed.w)
-        assert torch.cuda.mem_get_info()[0] > copy   # the copy would have fitted
-        out = []
-        for case in (packed, rows):
-            _check(case, cfg, 7400, 77, 16, 6)
-            kv = case.new_kv()
-            case.synthetic_context(kv, 7401, 77)
-            toks, par = synth.random_tree(7402, 16, 6, cfg.vocab)
-            out.append(case.step(kv, toks, par)[1])
-        assert np.array_equal(out[0].view(np.uint32), out[1].view(np.uint32))
+        kv = case.new_kv()
+        case.synthetic_context(kv, 7301, 77)
+        toks, par = synth.random_tree(7302, 16, 6, cfg.vocab)
+        before = case.step(kv, toks, par)[1]
+        for lay in case.dev.layers:
+            for k in ("wq", "wk", "wv", "wo", "w_gate", "w_up", "w_down"):
+                lay[k].mul_(1.25).add_(0.01)
+        case.dev.lm_head.neg_()
+        torch.cuda.synchronize()
+        after = case.step(kv, toks, par)[1]
+        fresh = dv.dv_verify_init(case.ccfg, case.dev.c)
+        want = torch.empty((16, cfg.vocab), dtype=torch.float32, device="cuda:0")
+        dv.dv_verify_step(fresh, toks, par, kv.c, want.data_ptr())
+        assert np.array_equal(after.view(np.uint32), want.cpu().numpy().view(np.uint32))
+        assert np.abs(after - before).max() > 0.1
     finally:
-        packed.close()
-        if rows is not None:
-            rows.close()
-        del fill
-        torch.cuda.empty_cache()
+        case.close()
+        if fresh is not None:
+            dv.dv_verify_free(fresh)
+
+
+@pytest.mark.parametrize("d,ffn", [(64, 16), (96 * 2, 48), (448, 1008), (320, 272)])
+def test_f32_odd_steps(d, ffn):
+    """Single last steps (an odd count of 16-column steps in the row or in a K
+    split), whose pair would reach past the row."""
+    cfg = small_cfg(n_layers=1, d_model=d, n_heads=d // 64, head_dim=64, d_ffn=ffn, vocab=96,
+                    init_std=0.09 * np.sqrt(256.0 / d))
+    case = GpuCase(cfg, seed=7600, capacity=64)
+    try:
+        for m in (1, 9, 33):
+            _check(case, cfg, 7700 + m, 20, m, 5 if m > 1 else 1)
+    finally:
+        case.close()
