@@ -90,3 +90,30 @@ def test_f32_odd_steps(d, ffn):
             _check(case, cfg, 7700 + m, 20, m, 5 if m > 1 else 1)
     finally:
         case.close()
+
+
+@pytest.mark.parametrize("d,m", [(1024, 8), (2048, 16), (2048, 33)])
+def test_f32_sums_are_eight_chains(d, m):
+    """Every projection sum is added up in 8 chains of K / 8 fp32 products (two
+    per wave).  A rounding is off by 0.42 2^-24 of the value (rms); over a chain
+    of n, whose partial sums grow with the square root of its length, by 0.3 2^-24
+    sqrt(n) of the result, and as much over 8 such chains.  The bar, on the
+    values of layer 0 against 64 bits, is 1.2 times that, with 2^-24 for the
+    norm; half as many chains miss it."""
+    cfg = small_cfg(n_layers=1, d_model=d, n_heads=d // 128, head_dim=128, d_ffn=64, vocab=96)
+    case = GpuCase(cfg, seed=7800, capacity=64)
+    try:
+        kv = case.new_kv()
+        toks, par = synth.random_tree(7801, m, 4, cfg.vocab)
+        case.step(kv, toks, par)
+        got = kv.layer_host(0, m)[1].astype(np.float64).transpose(1, 0, 2).reshape(m, d)
+        lay = case.w.layers[0]
+        x = case.w.embed[np.asarray(toks)].astype(np.float64)
+        u = x / np.sqrt((x * x).mean(1, keepdims=True) + cfg.rms_eps) * lay["attn_norm"].astype(np.float64)
+        want = u @ lay["wv"].astype(np.float64).T
+        err = np.linalg.norm(got - want) / np.linalg.norm(want)
+        bar = 1.2 * 2.0 ** -24 * np.sqrt(0.3 ** 2 * d / 8 + 1)
+        print("[f32] K = %d, %d nodes: %.3g, bar %.3g" % (d, m, err, bar), flush=True)
+        assert err <= bar
+    finally:
+        case.close()
