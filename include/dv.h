@@ -286,8 +286,9 @@ int dv_kv_commit(dv_handle *h, dv_kv *kv, const dv_accept *accept);
  * committed entries and commits all of them (kv->len += n).  With bf16 or
  * int8 weights and n > max_tree the prompt runs as causal chunks of up to 1024
  * tokens (an MFMA GEMM with fused epilogues for the projections, a causal
- * attention kernel);
- * otherwise as chains of at most max_tree tokens through the verify step's
+ * attention kernel), in a workspace that the handle's first such prompt
+ * allocates (about 16 d_model + 4 d_ffn bytes per token of a chunk);
+ * otherwise, and where that allocation fails, as chains of at most max_tree tokens through the verify step's
  * kernels.  out_next_token (host, nullable) receives the argmax after the
  * last prompt token, the root of the first draft tree.  Synchronises the
  * stream.  Errors: DV_EINVAL, DV_ECAPACITY, DV_EHIP. */

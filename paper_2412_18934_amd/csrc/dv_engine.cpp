@@ -561,7 +561,8 @@ bool pf_supported(const dv_handle *h)
 
 // The workspace is one allocation (a new handle's first prefill pays for it),
 // with the split-K part only where prefills run (the draft needs the rows
-// only).  Nothing but the counters has to start at zero: rows past the chunk's
+// only).  A failed allocation keeps the old one, and nothing else changes.
+// Nothing but the counters has to start at zero: rows past the chunk's
 // tokens are computed with, but every token's column stays its own and theirs
 // are dropped.
 int pf_reserve(dv_handle *h, int tokens, bool split)
@@ -570,10 +571,6 @@ int pf_reserve(dv_handle *h, int tokens, bool split)
     if (h->pf_cap >= cap && (h->pf_part || !split)) return DV_OK;
     split = split || h->pf_part;
     const dv_config &c = h->cfg;
-    if (h->pf_block) (void)hipFree(h->pf_block);
-    h->pf_block = nullptr;
-    h->pf_part = nullptr;
-    h->pf_cap = 0;
     const size_t Mc = cap, d = c.d_model, F = std::max(c.d_ffn, 1);
     const size_t cnt_bytes = DV_PF_MAX_TILES * 4;
     size_t total = 0;
@@ -586,8 +583,10 @@ int pf_reserve(dv_handle *h, int tokens, bool split)
                  o_us = take(Mc * d * 4), o_as = take(Mc * d * 4), o_hs = take(Mc * F * 4),
                  o_cnt = take(split ? cnt_bytes : 0), o_part = take(split ? (size_t)DV_PF_PART_TILES * 1024 : 0);
     char *b = nullptr;
-    if (hipMalloc((void **)&b, total) != hipSuccess)
+    if (hipMalloc((void **)&b, total) != hipSuccess) {
+        (void)hipGetLastError();  // or the next launch would report it
         return set_err(h, DV_ENOMEM, "prefill workspace for %d tokens: allocation failed", tokens);
+    }
     // (on the handle's stream: the GEMMs that count follow there, and a
     // non-blocking stream does not wait for the null stream)
     const hipError_t e = split ? hipMemsetAsync(b + o_cnt, 0, cnt_bytes, h->stream) : hipSuccess;
@@ -595,6 +594,7 @@ int pf_reserve(dv_handle *h, int tokens, bool split)
         (void)hipFree(b);
         return hip_fail(h, e, "prefill workspace clear");
     }
+    if (h->pf_block) (void)hipFree(h->pf_block);
     h->pf_block = b;
     h->pf_tok = (int32_t *)(b + o_tok);
     h->pf_x = (float *)(b + o_x);
@@ -609,13 +609,13 @@ int pf_reserve(dv_handle *h, int tokens, bool split)
     return DV_OK;
 }
 
+// (the workspace is reserved)
 int prefill_large(dv_handle *h, const int32_t *tokens, int n, dv_kv *kv, int32_t *out_next_token)
 {
     const dv_config &c = h->cfg;
     const int d = c.d_model, F = c.d_ffn, H = c.n_heads, hd = c.head_dim;
     hipStream_t s = h->stream;
-    int rc = pf_reserve(h, std::min(n, DV_PF_CHUNK), true);
-    if (rc) return rc;
+    int rc;
     auto ck = [&](hipError_t e, const char *what) -> int { return e == hipSuccess ? DV_OK : hip_fail(h, e, what); };
     const size_t layer_kv = (size_t)H * kv->capacity * hd;
     const bool q8 = h->wkind == W_I8;
@@ -1500,9 +1500,13 @@ int dv_prefill(dv_handle *h, const int32_t *tokens, int32_t n, dv_kv *kv, int32_
         return set_err(h, DV_ECAPACITY, "prompt of %d does not fit (len %d, capacity %d, max_ctx %d)",
                        n, kv->len, kv->capacity, h->cfg.max_ctx);
     if (pf_supported(h) && n > h->cfg.max_tree) {
-        rc = prefill_large(h, tokens, n, kv, out_next_token);
-        h->pending = false;
-        return rc;
+        // without room for its workspace the prompt runs as chains, which need none
+        rc = pf_reserve(h, std::min(n, DV_PF_CHUNK), true);
+        if (rc == DV_OK) {
+            rc = prefill_large(h, tokens, n, kv, out_next_token);
+            h->pending = false;
+        }
+        if (rc != DV_ENOMEM) return rc;
     }
     const int chunk = h->cfg.max_tree;
     int32_t parents[DV_MAX_TREE], pos[DV_MAX_TREE], depth[DV_MAX_TREE];

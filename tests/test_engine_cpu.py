@@ -84,6 +84,28 @@ def test_clears_are_ordered_before_the_launches(engine):
     assert [w for w, _, _ in engine.log()].count("pf_gemm") == 4 * 2
 
 
+def test_prefill_without_room_for_its_workspace(engine):
+    """The prompt runs as chains then, and the failed allocation leaves nothing
+    behind: no error for the next launch, and the workspace is made later."""
+    live = engine.lib.stub_live()
+    assert engine.prefill(300, fail_at=1 << 16) == 0
+    names = [w for w, _, _ in engine.log()]
+    assert engine.kv.len == 300 and "pf_gemm" not in names and names.count("accept") == 1
+    assert names.count("attention") == 2 * -(-300 // 8)
+    assert engine.lib.stub_live() == live
+    engine.kv.len = 0
+    assert engine.prefill(300) == 0
+    assert [w for w, _, _ in engine.log()].count("pf_gemm") == 4 * 2
+    # a longer prompt that needs more than there is keeps what it has
+    live = engine.lib.stub_live()
+    engine.kv.len = 0
+    assert engine.prefill(1000, fail_at=1 << 16) == 0 and engine.kv.len == 1000
+    assert engine.lib.stub_live() == live
+    engine.kv.len = 0
+    assert engine.prefill(300, fail_at=1 << 16) == 0
+    assert [w for w, _, _ in engine.log()].count("pf_gemm") == 4 * 2
+
+
 def test_fp32_weights_are_not_copied(lib):
     d, ffn, vocab, layers = 1024, 2816, 8192, 4
     e = Engine(lib, dv.DV_F32, n_layers=layers, d=d, ffn=ffn, vocab=vocab, max_ctx=64)
