@@ -73,7 +73,7 @@ struct dv_handle {
     float *logits_ws = nullptr;  // [max_tree][vocab] logits of a sampled step without out_logits
     // large-M prefill (allocated at its first use, sized for pf_cap tokens,
     // a multiple of 128; pf_part and pf_cnt for the split-K units of any
-    // chunk): residual stream, rotated queries, the split-layout
+    // chunk of up to that many): residual stream, rotated queries, the split-layout
     // operands (norm numerators, attention output, SwiGLU output) and the
     // norms' sums of squares over 64-row slices
     int pf_cap = 0;
@@ -94,7 +94,7 @@ struct dv_handle {
     float *feat_a = nullptr, *feat_b = nullptr;  // [DV_TREE_MAX + 1][d] draft features (row 64: the root's input)
     int32_t *tk_tok = nullptr, *tk_tok_h = nullptr;
     float *tk_p = nullptr, *tk_p_h = nullptr;
-    float *p_ws = nullptr;       // [2][vocab] current / residual distribution of the sampling walk
+    float *p_ws = nullptr;       // [2][vocab] current / residual distribution of the one-workgroup sampling walk
     GemmPlan p_qkv, p_o, p_gu, p_down, p_lm;
     int n_cu = 256;
 
@@ -559,6 +559,32 @@ bool pf_supported(const dv_handle *h)
            pf_addressable(c.d_model / 16, c.d_ffn, h->wkind == W_I8);
 }
 
+// The cuts of a chunk's projections: QKV, O, gate/up, down.
+struct PfPlans {
+    PfPlan qkv, o, gu, down;
+};
+
+PfPlans pf_plans(const dv_handle *h, int MT)
+{
+    const int d = h->cfg.d_model, F = h->cfg.d_ffn;
+    const bool q8 = h->wkind == W_I8;
+    return {pf_plan(3 * d / 16, MT, d, q8, h->n_cu), pf_plan(d / 16, MT, d, q8, h->n_cu),
+            pf_plan(F / 8, MT, d, q8, h->n_cu), pf_plan(d / 16, MT, F, q8, h->n_cu)};
+}
+
+// What the split-K units of any chunk of up to `tokens` tokens write.
+size_t pf_part_bytes(const dv_handle *h, int tokens)
+{
+    const int d = h->cfg.d_model, F = h->cfg.d_ffn;
+    int tiles = 0;
+    for (int MT = DV_PF_MIN_TILES; MT <= std::max(ceil_div(tokens, 16), DV_PF_MIN_TILES); ++MT) {
+        const PfPlans p = pf_plans(h, MT);
+        tiles = std::max({tiles, pf_part_tiles(3 * d / 16, p.qkv), pf_part_tiles(d / 16, p.o), pf_part_tiles(F / 8, p.gu),
+                          pf_part_tiles(d / 16, p.down)});
+    }
+    return (size_t)tiles * 1024;
+}
+
 // The workspace is one allocation (a new handle's first prefill pays for it),
 // with the split-K part only where prefills run (the draft needs the rows
 // only).  A failed allocation keeps the old one, and nothing else changes.
@@ -581,7 +607,7 @@ int pf_reserve(dv_handle *h, int tokens, bool split)
     };
     const size_t o_tok = take(Mc * 4), o_x = take(Mc * d * 4), o_q = take(Mc * d * 4), o_ssq = take(Mc * (d / 64 + 1) * 4),
                  o_us = take(Mc * d * 4), o_as = take(Mc * d * 4), o_hs = take(Mc * F * 4),
-                 o_cnt = take(split ? cnt_bytes : 0), o_part = take(split ? (size_t)DV_PF_PART_TILES * 1024 : 0);
+                 o_cnt = take(split ? cnt_bytes : 0), o_part = take(split ? pf_part_bytes(h, cap) : 0);
     char *b = nullptr;
     if (hipMalloc((void **)&b, total) != hipSuccess) {
         (void)hipGetLastError();  // or the next launch would report it
@@ -649,8 +675,7 @@ int prefill_large(dv_handle *h, const int32_t *tokens, int n, dv_kv *kv, int32_t
         base.x = h->pf_x;
         base.us = h->pf_us;
         base.ssq_out = h->pf_ssq;
-        const PfPlan plan_qkv = pf_plan(3 * d / 16, MT, d, q8, h->n_cu), plan_o = pf_plan(d / 16, MT, d, q8, h->n_cu),
-                     plan_gu = pf_plan(F / 8, MT, d, q8, h->n_cu), plan_down = pf_plan(d / 16, MT, F, q8, h->n_cu);
+        const PfPlans plan = pf_plans(h, MT);
         auto gemm = [&](const PfPlan &p, int epi, const uint16_t *packed, const float *scale, int rows, int K,
                         const uint16_t *xs, const void *gain) -> int {
             PfArgs a = base;
@@ -671,16 +696,16 @@ int prefill_large(dv_handle *h, const int32_t *tokens, int n, dv_kv *kv, int32_t
             const LayerW &w = h->layers[l];
             base.kc = static_cast<uint16_t *>(kv->k) + (size_t)l * layer_kv;
             base.vc = static_cast<uint16_t *>(kv->v) + (size_t)l * layer_kv;
-            if ((rc = gemm(plan_qkv, EPI_QKV, w.pk_qkv, w.ps_qkv, 3 * d, d, h->pf_us, nullptr))) return rc;
+            if ((rc = gemm(plan.qkv, EPI_QKV, w.pk_qkv, w.ps_qkv, 3 * d, d, h->pf_us, nullptr))) return rc;
             prof_begin(h, DV_K_ATTN);
             rc = ck(launch_attn_causal(h->pf_q, base.kc, base.vc, M, P0, H, hd, kv->capacity, MT, h->pf_as, s),
                     "causal attention");
             prof_end(h);
             if (rc) return rc;
-            if ((rc = gemm(plan_o, EPI_RESID, w.pk_o, w.ps_o, d, d, h->pf_as, w.ffn_norm))) return rc;
-            if ((rc = gemm(plan_gu, EPI_SWIGLU, w.pk_gu, w.ps_gu, 2 * F, d, h->pf_us, nullptr))) return rc;
+            if ((rc = gemm(plan.o, EPI_RESID, w.pk_o, w.ps_o, d, d, h->pf_as, w.ffn_norm))) return rc;
+            if ((rc = gemm(plan.gu, EPI_SWIGLU, w.pk_gu, w.ps_gu, 2 * F, d, h->pf_us, nullptr))) return rc;
             const void *next_gain = l + 1 < c.n_layers ? h->layers[l + 1].attn_norm : h->final_norm;
-            if ((rc = gemm(plan_down, EPI_RESID, w.pk_down, w.ps_down, d, F, h->pf_hs, next_gain))) return rc;
+            if ((rc = gemm(plan.down, EPI_RESID, w.pk_down, w.ps_down, d, F, h->pf_hs, next_gain))) return rc;
         }
         const bool last = done + M == n;
         if (last) {
@@ -986,7 +1011,7 @@ int dv_verify_init(const dv_config *cfg, const dv_weights *w, void *stream, dv_h
               dalloc((void **)&h->rope_cos, (size_t)c.max_ctx * (hd / 2) * 4) &&
               dalloc((void **)&h->rope_sin, (size_t)c.max_ctx * (hd / 2) * 4) &&
               dalloc((void **)&h->logits_ws, (size_t)c.max_tree * c.vocab * 4) &&
-              dalloc((void **)&h->p_ws, (size_t)2 * c.vocab * 4);
+              (sample_by_node(c.vocab) || dalloc((void **)&h->p_ws, (size_t)2 * c.vocab * 4));
     h->h_sd = new StepDesc();
     ok = ok && hipHostMalloc((void **)&h->h_acc, sizeof(DevAccept), hipHostMallocMapped | hipHostMallocCoherent) == hipSuccess &&
          hipHostGetDevicePointer((void **)&h->d_acc, h->h_acc, 0) == hipSuccess;

@@ -234,7 +234,8 @@ hipError_t noalloc_scratch(void **out);
 // ([Mp][d / 64]).
 #define DV_PF_MIN_TILES 3
 // 1 KB partial tiles (16 rows x 16 tokens) that the split-K units of one
-// prefill GEMM may write
+// prefill GEMM may write at most; the workspace holds what the model's own
+// plans write (pf_part_tiles)
 #define DV_PF_PART_TILES 65536
 #define DV_PF_MAX_TILES 1024  // split tiles that fit in there (2 or more units of 32 or more)
 struct PfArgs {
@@ -282,6 +283,8 @@ struct PfPlan {
     int shape, tt, n_tt, ks;
 };
 PfPlan pf_plan(int NB, int MT, int K, bool q8, int n_cu);
+// partial tiles of a GEMM of NB blocks cut like that (0 without K ranges)
+int pf_part_tiles(int NB, const PfPlan &p);
 // the prefill GEMM addresses a matrix with 31-bit byte offsets
 inline bool pf_addressable(int NB, int K, bool q8) { return (double)NB * K * (q8 ? 16 : 32) < 2147483648.0; }
 // Whether a bf16 projection of NB blocks without K splits, over a verify step's

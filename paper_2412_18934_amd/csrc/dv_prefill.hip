@@ -876,6 +876,12 @@ PfPlan pf_plan(int NB, int MT, int K, bool q8, int n_cu)
     return best;
 }
 
+int pf_part_tiles(int NB, const PfPlan &p)
+{
+    const int rows = 4 * SHAPE_NWR[p.shape];  // blocks of a unit
+    return p.ks > 1 ? (NB + rows - 1) / rows * p.n_tt * p.ks * rows * p.tt : 0;
+}
+
 hipError_t launch_pf_gemm(const PfArgs &a, const PfPlan &p, int epi, hipStream_t s)
 {
     if (a.K % (a.scale ? 64 : 32) || a.NB < 1 || a.MT < 1 || a.d % 64 || a.M < 1 || a.M > 16 * a.MT || a.n_tt != p.n_tt ||

@@ -53,6 +53,12 @@ def part_tiles(nb, p):
     return units(nb, p) * SHAPE_NWR[p.shape] * 4 * p.tt if p.ks > 1 else 0
 
 
+def library_part_tiles(nb, p):
+    f = dv.lib()._Z13pf_part_tilesiRK6PfPlan
+    f.restype, f.argtypes = ctypes.c_int, [ctypes.c_int, ctypes.POINTER(PfPlan)]
+    return f(nb, ctypes.byref(p))
+
+
 def launch(args, p, epi):
     f = dv.lib()._Z14launch_pf_gemmRK6PfArgsRK6PfPlaniP12ihipStream_t
     f.restype, f.argtypes = ctypes.c_int, [ctypes.POINTER(PfArgs), ctypes.POINTER(PfPlan), ctypes.c_int,

@@ -106,6 +106,27 @@ def test_prefill_without_room_for_its_workspace(engine):
     assert [w for w, _, _ in engine.log()].count("pf_gemm") == 4 * 2
 
 
+def test_workspaces_are_what_the_calls_use(lib):
+    """The split-K partials are sized by the model's plans, and the rows of the
+    one-workgroup sampling walk exist only for vocabularies that take it."""
+    e = Engine(lib, dv.DV_BF16)
+    try:
+        small = lib.stub_live()
+        assert e.prefill(1000) == 0
+        # 63 tiles in 8 groups, d_model / 16 = 16 blocks and 3 or 5.5 times that, 2 ranges
+        rows = 1024 * (4 * 256 * 4 + 704 * 4 + 4 * 5 + 4)
+        part = 1024 * 96 * 8 * 2 * 8
+        assert rows <= lib.stub_live() - small <= rows + part + (1 << 16)
+    finally:
+        e.close()
+    allocations = []
+    for vocab in (65536, 65568):
+        e = Engine(lib, dv.DV_BF16, n_layers=1, vocab=vocab)
+        allocations.append(sum(w == "malloc" for w, _, _ in e.init_log))
+        e.close()
+    assert allocations[1] == allocations[0] + 1
+
+
 def test_fp32_weights_are_not_copied(lib):
     d, ffn, vocab, layers = 1024, 2816, 8192, 4
     e = Engine(lib, dv.DV_F32, n_layers=layers, d=d, ffn=ffn, vocab=vocab, max_ctx=64)

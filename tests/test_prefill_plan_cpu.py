@@ -2,7 +2,8 @@
 kernel is built for, and fits the split-K workspace."""
 import pytest
 
-from tests.pf_gemm import MAX_TILES, MIN_TILES, PART_TILES, SHAPE_NWR, part_tiles, plan, tiles_per_group, units
+from tests.pf_gemm import (MAX_TILES, MIN_TILES, PART_TILES, SHAPE_NWR, library_part_tiles, part_tiles, plan,
+                           tiles_per_group, units)
 
 
 @pytest.mark.parametrize("n_cu", [256, 64])
@@ -23,5 +24,6 @@ def test_plans_are_valid(d, ffn, n_cu):
                 # every K group of every range has a step
                 steps, nkg = k // (64 if q8 else 32), 8 // SHAPE_NWR[p.shape]
                 assert p.ks == 1 or p.ks * nkg <= steps
+                assert library_part_tiles(nb, p) == part_tiles(nb, p)
                 if p.ks > 1:
                     assert part_tiles(nb, p) <= PART_TILES and units(nb, p) // p.ks <= MAX_TILES
