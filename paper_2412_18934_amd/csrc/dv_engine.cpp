@@ -698,7 +698,7 @@ int prefill_large(dv_handle *h, const int32_t *tokens, int n, dv_kv *kv, int32_t
             base.vc = static_cast<uint16_t *>(kv->v) + (size_t)l * layer_kv;
             if ((rc = gemm(plan.qkv, EPI_QKV, w.pk_qkv, w.ps_qkv, 3 * d, d, h->pf_us, nullptr))) return rc;
             prof_begin(h, DV_K_ATTN);
-            rc = ck(launch_attn_causal(h->pf_q, base.kc, base.vc, M, P0, H, hd, kv->capacity, MT, h->pf_as, s),
+            rc = ck(launch_attn_causal(h->pf_q, base.kc, base.vc, M, P0, H, hd, kv->capacity, MT, h->n_cu, h->pf_as, s),
                     "causal attention");
             prof_end(h);
             if (rc) return rc;

@@ -307,7 +307,7 @@ constexpr PfPlan PF_STEP_PLAN{2, 4, 1, 1};
 hipError_t launch_pf_gemm(const PfArgs &a, const PfPlan &p, int epi, hipStream_t s);
 // causal attention of the chunk; output in split layout (MT token tiles)
 hipError_t launch_attn_causal(const float *q, const void *kc, const void *vc, int M, int P0, int H, int hd, int cap,
-                              int MT, uint16_t *out, hipStream_t s);
+                              int MT, int n_cu, uint16_t *out, hipStream_t s);
 
 // Draft side
 #define DV_TOPK_MAX 16

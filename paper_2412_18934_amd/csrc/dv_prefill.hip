@@ -770,7 +770,7 @@ hipError_t launch_pf_embed(const int32_t *tokens, const void *embed, int M, int 
 namespace {
 
 // Workgroup shapes: rows per unit and K groups; a shape's steps in flight are
-// what its registers hold (8 waves of 256 VGPRs; only int8 QKV at 128 rows and 8
+// what its registers hold (8 waves of 256 VGPRs; only int8 QKV at 256 rows and 8
 // tiles spills, two address registers reloaded per step).
 constexpr int SHAPE_NWR[3] = {8, 4, 2};
 constexpr int PF_TT_MIN = 4, PF_TT_MAX = 8, PF_KS_MAX = 8;
@@ -828,7 +828,11 @@ hipError_t pf_launch_epi(const PfArgs &a, int shape, int tt, hipStream_t s)
 // every CU; large ones lose to them by the partials' traffic.  The constants
 // are a fit to 2900 launches on random data at (d_model, d_ffn) = (4096,
 // 11008) and (5120, 13824), 5 to 64 token tiles, every cut: the chosen one is
-// 1% slower than the fastest on average, 6% at most.  Before, 512 x
+// 1% slower than the fastest on average, 6% at most.  At widths it was not fitted to
+// (1024, 2048, 3072, 8192; 3 to 64 tiles; event-timed launches, every cut) it is 2-4%
+// behind on average in bf16 and 0.4-7% in int8: small matrices get too few K
+// ranges (worst: int8 gate/up at 2048 x 5504, 48 tokens, 30 us, with 4 ranges 21).
+// Before, 512 x
 // 128 (QKV, gate/up) and 512 x 48 tiles (O, down) ran over all of K, with the
 // B operands read just before use.  160 tokens, 7B width, us: QKV 168 -> 50,
 // O 84 -> 30, gate/up 170 -> 75, down 206 -> 49 (38 and 57 for O and down while
@@ -913,14 +917,14 @@ static hipError_t causal_launch(int nkg, const float *q, const void *kc, const v
 }
 
 hipError_t launch_attn_causal(const float *q, const void *kc, const void *vc, int M, int P0, int H, int hd, int cap,
-                              int MT, uint16_t *out, hipStream_t s)
+                              int MT, int n_cu, uint16_t *out, hipStream_t s)
 {
     // Two key groups while the query blocks do not fill the CUs, and up to two
     // workgroups per CU when the prompt is most of the keys (the query blocks
     // are then uneven and the longest one sets the time); 280 workgroups of 29
     // to 41 tiles each: 71 us with one group, 75 with two.
     const int wgs = H * ((M + 63) / 64), tiles = (P0 + M + 31) / 32;
-    const int nkg = tiles >= 4 && (wgs <= 256 || (wgs <= 512 && P0 <= M)) ? 2 : 1;
+    const int nkg = tiles >= 4 && (wgs <= n_cu || (wgs <= 2 * n_cu && P0 <= M)) ? 2 : 1;
     if (hd == 128) return causal_launch<128>(nkg, q, kc, vc, M, P0, H, cap, MT, out, s);
     if (hd == 64) return causal_launch<64>(nkg, q, kc, vc, M, P0, H, cap, MT, out, s);
     return hipErrorInvalidValue;

@@ -95,7 +95,7 @@ hipError_t launch_pf_embed(const int32_t *, const void *, int, int, int, const v
 PfPlan pf_plan(int, int MT, int, bool, int) { return PfPlan{1, MT > 8 ? 8 : (MT < 4 ? 4 : MT), (MT + 7) / 8, 2}; }
 int pf_part_tiles(int NB, const PfPlan &p) { return (NB + 15) / 16 * p.n_tt * p.ks * 16 * p.tt; }
 hipError_t launch_pf_gemm(const PfArgs &, const PfPlan &, int, hipStream_t s) { return launched("pf_gemm", s); }
-hipError_t launch_attn_causal(const float *, const void *, const void *, int, int, int, int, int, int, uint16_t *, hipStream_t s)
+hipError_t launch_attn_causal(const float *, const void *, const void *, int, int, int, int, int, int, int, uint16_t *, hipStream_t s)
 {
     return launched("causal", s);
 }
