@@ -16,8 +16,8 @@
 //                    in one workgroup, for the largest vocabularies
 //   k_kv_commit      in-place compaction of the accepted path
 //
-// Weights are bf16 or fp32, activations and accumulation fp32.  Every
-// reduction runs in a fixed order, so results are bitwise reproducible.
+// Weights are bf16, int8 with row scales, or fp32; activations and accumulation
+// fp32.  Every reduction runs in a fixed order, so results are bitwise reproducible.
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 #include <math.h>
@@ -1521,9 +1521,9 @@ __global__ __launch_bounds__(64 * NW) void k_attn_mfma(AttnArgs a)
     // waits) merges the splits of every node in split order: a softmax-
     // weighted sum with a running maximum (base-2 units), then the output in
     // split layout, 8 dims of one node per thread.
-    // (the partials were published without waiting for the stores: the
-    // merging split reloads any value that still holds the empty-slot
-    // pattern, and empties every slot it read for the next launch)
+    // Every split waits for its own stores before it counts itself, so the
+    // merging one finds all partials complete and loads each once (unlike the
+    // projections' fold, no slot holds an empty pattern here).
     __shared__ int last_s;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();

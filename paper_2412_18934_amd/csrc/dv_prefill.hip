@@ -10,8 +10,8 @@
 #include "dv_internal.h"
 
 // ---------------------------------------------------------------------------
-// Large-M prefill: a prompt chunk of M tokens (padded to Mp, a multiple of
-// 128) in one causal pass.  The projections are a dense contraction here, so
+// Large-M prefill: a prompt chunk of M tokens (padded to Mp, a multiple of 16
+// and at least 48) in one causal pass.  The projections are a dense contraction here, so
 // they run on an MFMA GEMM over the packed weights of the verify path (block
 // (k-step s, 16-row block gb) at (s NB + gb) 512) and split-layout
 // activations of the whole chunk (MT = Mp / 16 token tiles), with the verify
