@@ -284,7 +284,8 @@ int dv_kv_commit(dv_handle *h, dv_kv *kv, const dv_accept *accept);
  * draft round, Section 3.1; the Limitations section names long-context
  * prefill as the method's bottleneck): appends the K/V of tokens[0..n) after the kv->len
  * committed entries and commits all of them (kv->len += n).  With bf16 or
- * int8 weights and n > max_tree the prompt runs as causal chunks of up to 1024
+ * int8 weights and n > max_tree (int8: and where that is estimated to be faster;
+ * it is for more than four chains) the prompt runs as causal chunks of up to 1024
  * tokens (an MFMA GEMM with fused epilogues for the projections, a causal
  * attention kernel), in a workspace that the handle's first such prompt
  * allocates (about 16 d_model + 4 d_ffn bytes per token of a chunk);

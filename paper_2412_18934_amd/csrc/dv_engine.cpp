@@ -559,6 +559,33 @@ bool pf_supported(const dv_handle *h)
            pf_addressable(c.d_model / 16, c.d_ffn, h->wkind == W_I8);
 }
 
+// Whether an int8 prompt of a few chains is faster as chains through the verify
+// kernels.  They read the weights once per chain, but have fewer and smaller
+// launches, and their attention splits the keys over workgroups, where a causal
+// pass walks all of them in one.  Both times are estimated, us per layer, with W 10^6
+// weights, k 10^6 key and value bytes and t 16-token tiles:
+//   chains  37 + 0.173 W + 0.30 k + (t - 1) (12.9 + 0.089 W) each
+//   causal  65 + 0.163 W + t (4.15 + 0.040 W), and 0.41 + 1.03 hd / 128 per 32 keys
+//           of a key group and round of workgroups
+// a fit to 260 prompts of 2 to 4 chains (d_model 256 to 6144, max_tree 1 to 64, 0
+// to 12000 cached keys).  Over those the choice is 0.5% behind the faster one on average,
+// 19% at most (58 against 68 us); without it the causal pass took up to 2.4 times as long as
+// the chains (d_model 1536, 10 tokens behind 7909 keys: 115 and 272 us a layer).
+bool chains_faster(const dv_handle *h, int n, int P0)
+{
+    const dv_config &c = h->cfg;
+    const int chains = ceil_div(n, c.max_tree);
+    if (h->wkind != W_I8 || chains > 4) return false;
+    const double d = c.d_model, W = (4 * d * d + 3 * d * c.d_ffn) * 1e-6, k = 4 * d * (P0 + n) * 1e-6;
+    const int more = (chains - 1) * ceil_div(c.max_tree, 16) + ceil_div(n - (chains - 1) * c.max_tree, 16) - chains;
+    const double chain_us = chains * (37 + 0.173 * W + 0.30 * k) + more * (12.9 + 0.089 * W);
+    const int groups = causal_key_groups(n, P0, c.n_heads, h->n_cu), wgs = c.n_heads * ceil_div(n, 64);
+    const double walk = (double)ceil_div(P0 + n, 32) / groups * ceil_div(wgs, (groups == 2 ? 2 : 3) * h->n_cu);
+    const double causal_us = 65 + 0.163 * W + std::max(ceil_div(n, 16), DV_PF_MIN_TILES) * (4.15 + 0.040 * W) +
+                             walk * (0.41 + 1.03 * c.head_dim / 128);
+    return chain_us < causal_us;
+}
+
 // The cuts of a chunk's projections: QKV, O, gate/up, down.
 struct PfPlans {
     PfPlan qkv, o, gu, down;
@@ -1524,7 +1551,7 @@ int dv_prefill(dv_handle *h, const int32_t *tokens, int32_t n, dv_kv *kv, int32_
     if ((long)kv->len + n > kv->capacity || (long)kv->len + n > h->cfg.max_ctx)
         return set_err(h, DV_ECAPACITY, "prompt of %d does not fit (len %d, capacity %d, max_ctx %d)",
                        n, kv->len, kv->capacity, h->cfg.max_ctx);
-    if (pf_supported(h) && n > h->cfg.max_tree) {
+    if (pf_supported(h) && n > h->cfg.max_tree && !chains_faster(h, n, kv->len)) {
         // without room for its workspace the prompt runs as chains, which need none
         rc = pf_reserve(h, std::min(n, DV_PF_CHUNK), true);
         if (rc == DV_OK) {

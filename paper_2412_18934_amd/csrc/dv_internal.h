@@ -305,6 +305,15 @@ constexpr PfPlan PF_STEP_PLAN{2, 4, 1, 1};
 // the prefill GEMM with the EPI_QKV, EPI_SWIGLU or EPI_RESID epilogue, or
 // EPI_LOGITS with PF_STEP_PLAN
 hipError_t launch_pf_gemm(const PfArgs &a, const PfPlan &p, int epi, hipStream_t s);
+// Key groups of the causal attention's workgroups: two while the query blocks do
+// not fill the CUs, and up to two workgroups per CU when the prompt is most of the
+// keys (the query blocks are then uneven and the longest one sets the time); 280
+// workgroups of 29 to 41 tiles each: 71 us with one group, 75 with two.
+inline int causal_key_groups(int M, int P0, int H, int n_cu)
+{
+    const int wgs = H * ((M + 63) / 64), tiles = (P0 + M + 31) / 32;
+    return tiles >= 4 && (wgs <= n_cu || (wgs <= 2 * n_cu && P0 <= M)) ? 2 : 1;
+}
 // causal attention of the chunk; output in split layout (MT token tiles)
 hipError_t launch_attn_causal(const float *q, const void *kc, const void *vc, int M, int P0, int H, int hd, int cap,
                               int MT, int n_cu, uint16_t *out, hipStream_t s);

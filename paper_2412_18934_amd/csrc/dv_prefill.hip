@@ -919,12 +919,7 @@ static hipError_t causal_launch(int nkg, const float *q, const void *kc, const v
 hipError_t launch_attn_causal(const float *q, const void *kc, const void *vc, int M, int P0, int H, int hd, int cap,
                               int MT, int n_cu, uint16_t *out, hipStream_t s)
 {
-    // Two key groups while the query blocks do not fill the CUs, and up to two
-    // workgroups per CU when the prompt is most of the keys (the query blocks
-    // are then uneven and the longest one sets the time); 280 workgroups of 29
-    // to 41 tiles each: 71 us with one group, 75 with two.
-    const int wgs = H * ((M + 63) / 64), tiles = (P0 + M + 31) / 32;
-    const int nkg = tiles >= 4 && (wgs <= n_cu || (wgs <= 2 * n_cu && P0 <= M)) ? 2 : 1;
+    const int nkg = causal_key_groups(M, P0, H, n_cu);
     if (hd == 128) return causal_launch<128>(nkg, q, kc, vc, M, P0, H, cap, MT, out, s);
     if (hd == 64) return causal_launch<64>(nkg, q, kc, vc, M, P0, H, cap, MT, out, s);
     return hipErrorInvalidValue;

@@ -34,7 +34,8 @@ def lib(tmp_path_factory):
 class Engine:
     def __init__(self, lib, dtype, n_layers=2, d=256, ffn=704, vocab=1024, max_ctx=4096, max_tree=8, stream=STREAM):
         self.lib = lib
-        cfg = dv.dv_config(n_layers=n_layers, d_model=d, n_heads=d // 64, head_dim=64, d_ffn=ffn, vocab=vocab,
+        hd = 128 if d >= 1024 else 64
+        cfg = dv.dv_config(n_layers=n_layers, d_model=d, n_heads=d // hd, head_dim=hd, d_ffn=ffn, vocab=vocab,
                            rms_eps=1e-6, rope_base=10000.0, weight_dtype=dtype, max_ctx=max_ctx, max_tree=max_tree)
         tab = ctypes.cast((ctypes.c_void_p * n_layers)(*([0x1000] * n_layers)), ctypes.POINTER(ctypes.c_void_p))
         w = dv.dv_weights(0x1000, 0x1000, 0x1000, *[tab] * 9, 0x1000, *[tab] * 7)
@@ -104,6 +105,26 @@ def test_prefill_without_room_for_its_workspace(engine):
     engine.kv.len = 0
     assert engine.prefill(300, fail_at=1 << 16) == 0
     assert [w for w, _, _ in engine.log()].count("pf_gemm") == 4 * 2
+
+
+@pytest.mark.parametrize("d,ffn,max_tree,n,kept,chains", [
+    (1536, 4224, 8, 10, 7909, True),      # a few tokens behind a long context
+    (1024, 2816, 64, 65, 4000, True), (1024, 2816, 4, 5, 0, True),
+    (1024, 2816, 64, 128, 0, False), (5120, 13824, 64, 65, 0, False), (5120, 13824, 64, 100, 2000, False),
+    (1024, 2816, 8, 33, 4000, False),     # more than four chains
+])
+def test_int8_prompts_of_few_chains_take_the_faster_route(lib, d, ffn, max_tree, n, kept, chains):
+    """Measured on both routes, us per layer, chains and causal: 115 / 272, 157 /
+    217, 82 / 89, 171 / 113, 267 / 210, 363 / 301.  bf16 prompts take the causal
+    pass as they always did."""
+    for dtype in (dv.DV_I8, dv.DV_BF16):
+        e = Engine(lib, dtype, n_layers=1, d=d, ffn=ffn, vocab=32, max_ctx=8192, max_tree=max_tree)
+        e.kv.len = kept
+        assert e.prefill(n) == 0 and e.kv.len == kept + n
+        names = [w for w, _, _ in e.log()]
+        took_chains = "pf_gemm" not in names
+        assert took_chains == (chains and dtype == dv.DV_I8)
+        e.close()
 
 
 def test_workspaces_are_what_the_calls_use(lib):
