@@ -564,8 +564,17 @@ __global__ __launch_bounds__(16) void k_pack_scales(GemmArgs a, int epi, float *
     dst[gb * 16 + r] = sc[rm.row0[h] + r];
 }
 
+// Two waves per SIMD for the int8 residual projections of 17 to 32 nodes: left
+// to itself the compiler takes 275 registers, one workgroup per CU, and models whose
+// row groups and K splits make more units than CUs (d_model 3584: 280) then take two
+// rounds (two int8 layers, 24 nodes: 252 us, 241 with two).  0 leaves it to the compiler.
+template <int MT_, int EPI, int RB, bool Q8> constexpr int proj_min_waves()
+{
+    return Q8 && MT_ == 2 && EPI == EPI_RESID && RB == 4 ? 2 : 0;
+}
+
 template <int MT_, int EPI, typename KV, int NW, int U, int RB, bool Q8 = false>
-__global__ __launch_bounds__(64 * NW) void k_proj(GemmArgs a)
+__global__ __launch_bounds__(64 * NW, (proj_min_waves<MT_, EPI, RB, Q8>())) void k_proj(GemmArgs a)
 {
     constexpr bool HALF = MT_ == 0;
     constexpr int MT = HALF ? 1 : MT_;  // token tiles of the MFMA outputs

@@ -134,3 +134,12 @@ def test_int8_prefill_and_sampled_step(i8_case):
     out = torch.empty((10, case.cfg.vocab), device="cuda:0")
     dv.dv_verify_step_sampled(case.h, toks, par, kv.c, q.data_ptr(), 1.0, ua, ub, out.data_ptr())
     np.testing.assert_array_equal(out.cpu().numpy(), lg)
+
+
+@pytest.mark.parametrize("mt", [0, 1, 2])
+def test_residual_projections_run_two_workgroups_per_cu(mt):
+    """Their row groups and K splits can make more units than CUs (d_model 3584:
+    280), which then take two rounds if a CU holds only one of them."""
+    f = dv.lib()._Z18gemm_blocks_per_cuiiiii   # (epilogue, weight kind, packed, token tiles, blocks per group)
+    resid, i8 = 1, 2
+    assert f(resid, i8, 1, mt, 4) >= 2
