@@ -64,7 +64,6 @@ hipError_t hipDeviceSynchronize() { return note("devsync", nullptr), hipSuccess;
 hipError_t hipStreamSynchronize(hipStream_t s) { return note("sync", s), hipSuccess; }
 hipError_t hipGetDevice(int *d) { return *d = 0, hipSuccess; }
 hipError_t hipDeviceGetAttribute(int *v, hipDeviceAttribute_t, int) { return *v = 256, hipSuccess; }
-hipError_t hipMemGetInfo(size_t *f, size_t *t) { return *f = *t = (size_t)288 << 30, hipSuccess; }
 hipError_t hipGetLastError() { hipError_t e = g_err; return g_err = hipSuccess, e; }
 const char *hipGetErrorString(hipError_t) { return "stub"; }
 hipError_t hipEventCreate(hipEvent_t *) { return hipErrorNotSupported; }
