@@ -815,17 +815,19 @@ __global__ __launch_bounds__(64 * NW, (proj_min_waves<MT_, EPI, RB, Q8>())) void
 // nodes: 837 us, 515 with the turn).  A wave therefore takes steps in pairs and
 // loads a block's pair as 2 x 8 rows of 128 contiguous bytes, 8 lanes a row, and turns
 // it through LDS that only this wave uses (16-byte chunk c of row r at c ^ (r % 8),
-// so neither side has bank conflicts).  Units, K splits, the wave partials' sum
-// in LDS and the epilogues are k_proj's.
+// so neither side has bank conflicts).  Row groups start at different columns (5
+// pairs apart): in step with each other they would read rows a power of two apart, that
+// is from few of the memory channels (515 -> 454 us, K = 5120 509 -> 480).  Units, K
+// splits, the wave partials' sum in LDS and the epilogues are k_proj's.
 // A wave adds up columns 4 g, 4 g + 2 and 4 g + 1, 4 g + 3 in two chains: the 8
 // chains of a workgroup are as long as the VALU kernel's below, so the rounding
 // is its own (relative error of layer 0's keys, K = 4096: 4.2e-7, with one chain per
 // wave 5.8e-7; of the logits after two layers 1.8e-6, 2.4e-6).
 // 7B width, 16 tokens, against the VALU kernel it replaces (8 lanes per row,
-// every row's lanes loading the activations again): QKV 174 -> 43 us, O and
-// down together 381 -> 66, gate/up 243 -> 86, lm_head 318 -> 102 (4.7, 3.7, 4.2 and
-// 5.2 TB/s; a packed copy of the weights in lane order reaches 5.4 to 6.3, but
-// doubles their memory and does not follow the caller's writes).
+// every row's lanes loading the activations again): QKV 174 -> 37 us, O 106 ->
+// 19, gate/up 243 -> 72, down 275 -> 38, lm_head 318 -> 84 (5.4, 3.6, 5.0, 4.8 and
+// 6.2 TB/s).  A packed copy of the weights in lane order is no faster at 16 nodes
+// and 6% at 60, and would double their memory and miss the caller's writes.
 template <int MT, int EPI, int NW, int U, int RB>
 __global__ __launch_bounds__(64 * NW) void k_proj_f32(GemmArgs a)
 {
@@ -847,9 +849,14 @@ __global__ __launch_bounds__(64 * NW) void k_proj_f32(GemmArgs a)
     for (int unit = blockIdx.x; unit < a.n_units; unit += gridDim.x) {
         const int g = unit / KS, ks = unit - g * KS;
         const int sb = (ks * S) / KS, T = ((ks + 1) * S) / KS - sb;  // this unit's steps
-        // pairs of steps go round the waves: wave w has the pairs w, w + NW, ...
-        // (the unit's last pair may be a single step)
-        const int np = (T + 1) / 2, n = wave < np ? (np - wave + NW - 1) / NW : 0;
+        // pairs of steps go round the waves, from pair 5 g on: wave w has the pairs
+        // 5 g + w, 5 g + w + NW, ... modulo np (the unit's last pair, np - 1, may
+        // be a single step)
+        const int np = (T + 1) / 2, n = wave < np ? (np - wave + NW - 1) / NW : 0, p0 = 5 * g % np;
+        auto pair = [&](int i) {
+            const int q = p0 + wave + NW * i;
+            return q < np ? q : q - np;
+        };
         const int xlane = n16 * K + 4 * g4;
         const float *wp[RB];
 #pragma unroll
@@ -881,7 +888,7 @@ __global__ __launch_bounds__(64 * NW) void k_proj_f32(GemmArgs a)
             f32x4 wb[U][RB][2], xb[U][2][MT];
             auto fetch_w = [&](int j, int i) {
                 // (a single last step's other half may lie past the row)
-                int c = 16 * (sb + 2 * (wave + NW * i)) + 4 * (lane & 7);
+                int c = 16 * (sb + 2 * pair(i)) + 4 * (lane & 7);
                 c = c < K ? c : c - 16;
 #pragma unroll
                 for (int b = 0; b < RB; ++b)
@@ -893,7 +900,7 @@ __global__ __launch_bounds__(64 * NW) void k_proj_f32(GemmArgs a)
             auto fetch_x = [&](int j, int i) {
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
-                    const int st = min(sb + 2 * (wave + NW * i) + h, S - 1);
+                    const int st = min(sb + 2 * pair(i) + h, S - 1);
 #pragma unroll
                     for (int mt = 0; mt < MT; ++mt)
                         xb[j][h][mt] = *reinterpret_cast<const f32x4 *>(a.x + (size_t)(16 * mt) * K + 16 * st + xlane);
@@ -943,7 +950,7 @@ __global__ __launch_bounds__(64 * NW) void k_proj_f32(GemmArgs a)
                     stage(j);
                     fetch_w(j, min(i + j + U, n - 1));
                     mfma(j, 0);
-                    mfma(j, 1);
+                    if (2 * pair(i + j) + 1 < T) mfma(j, 1);
                     fetch_x(j, min(i + j + U, n - 1));
                     // keep pair j's loads ahead of pair j + 1's MFMAs
                     __builtin_amdgcn_sched_barrier(0);
@@ -954,7 +961,7 @@ __global__ __launch_bounds__(64 * NW) void k_proj_f32(GemmArgs a)
                 if (i + j >= n) break;
                 stage(j);
                 mfma(j, 0);
-                if (2 * (wave + NW * (i + j)) + 1 < T) mfma(j, 1);
+                if (2 * pair(i + j) + 1 < T) mfma(j, 1);
             }
         }
         if constexpr (EPI == EPI_RESID) {
